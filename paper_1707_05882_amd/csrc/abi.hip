@@ -139,6 +139,7 @@ struct vbrdf_plan : LaunchSet {
     if (ws_d && ws_owned) (void)hipFree(ws_d);
     if (status_d) (void)hipFree(status_d);
     if (order_d) (void)hipFree(const_cast<int32_t*>(order_d));
+    if (order_plan_d) (void)hipFree(const_cast<int32_t*>(order_plan_d));
     if (queue_d) (void)hipFree(queue_d);
     if (below_d) (void)hipFree(const_cast<int32_t*>(below_d));
     if (base_off_d) (void)hipFree(const_cast<int64_t*>(base_off_d));
@@ -434,15 +435,27 @@ vbrdf_status vbrdf_plan_create(const vbrdf_plan_desc* d, vbrdf_plan** out) {
   p->tasks_d = tasks_d;
   if (st == VBRDF_OK) st = upload(quad, &quad_d);
   p->quad_d = quad_d;
-  if (st == VBRDF_OK) {  // eigensolver work order: largest systems first (stable)
+  if (st == VBRDF_OK) {
+    // Eigensolver work orders. The low orders are the ones that the iteration for weakly coupled orders
+    // leaves (those below 16 hold all of them up to asymmetries of 0.9): they come first, so that they
+    // start at once and spread over the XCDs (in plain plan order the like orders of layers with 8 k
+    // orders fell on the same XCDs, 32 against 8 ms for 72 layers of 64 orders at N = 32).
     std::vector<int32_t> order(p->items_h.size());
     for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return p->items_h[a].n > p->items_h[b].n; });
-    int32_t* order_d = nullptr;
-    st = upload(order, &order_d);
-    p->order_d = order_d;
+    auto low = [&](int32_t i) { return p->items_h[i].m < 16; };
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return low(a) > low(b); });
+    int32_t* plan_d = nullptr;
+    st = upload(order, &plan_d);
+    p->order_plan_d = plan_d;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+      const int na = p->items_h[a].n, nb = p->items_h[b].n;
+      if ((na > kLdsMaxn) != (nb > kLdsMaxn)) return na > kLdsMaxn;
+      return low(a) != low(b) ? low(a) : na > nb;
+    });
     for (const Item& it : p->items_h) p->n_big += it.n > kLdsMaxn ? 1 : 0;
+    int32_t* order_d = nullptr;
+    if (st == VBRDF_OK) st = upload(order, &order_d);
+    p->order_d = order_d;
   }
   if (st == VBRDF_OK) {
     std::vector<int32_t> zero(1, 0);
@@ -567,6 +580,27 @@ namespace vbrdf {
 
 static void enqueue_stacks(const LaunchSet& ls, const double* base, int32_t* layer_status, hipStream_t s);
 
+// Whether the solve runs the iteration for weakly coupled orders first. It frees compute units, so it
+// pays where the general eigensolver would need more than one round of them (one problem per unit),
+// or where its problems contend for the memory (n > 256: 256 orders at n = 512 took 851 ms, with the
+// 10 strongly coupled ones left to it 443 ms); below that the strongly coupled orders bound the stage
+// either way and the iteration only delays them (64 orders at n = 128: 4.56 against 4.83 ms). Not with
+// a cap on the QR sweeps (a forced failure, which needs every order to go by the QR), and not where
+// the adjoint's state is kept: its gradients amplify the rounding of the eigenvectors of weak orders
+// (dF / d coefficient of the highest degrees is good to 1e-5 at N = 44), so they keep their rounding.
+static bool use_weak(const LaunchSet& ls) {
+  return ls.qr_sweep_cap == 0 && !ls.save && (ls.n_items > kWeakAboveItems || ls.max_n > 256);
+}
+
+// Panels of k_weak_eigen for the largest item. Sizes up to 256 use their widest panels below it too
+// (64 columns up to n = 128, 32 up to 256), so the largest number can be that of a smaller size.
+static int weak_panels_for(const LaunchSet& ls) {
+  int p = weak_panels(ls.max_n);
+  if (ls.max_n > 256) p = std::max(p, weak_panels(256));
+  if (ls.max_n > 128) p = std::max(p, weak_panels(128));
+  return p;
+}
+
 // The launch sequence of one solve on stream s; when evs is given, kNumSolveStages + 1 events are
 // recorded around and between the stages.
 void enqueue_solve(const LaunchSet& ls, const double* tau, const double* omega, const double* coef,
@@ -583,7 +617,8 @@ void enqueue_solve(const LaunchSet& ls, const double* tau, const double* omega, 
   mark();
   k_validate<<<p->n_layers, 64, 0, s>>>(p->layers_d, p->n_layers, tau, omega, coef, layer_status);
   mark();
-  k_legendre<<<ni, kLegThreads, 0, s>>>(p->items_d, p->layers_d, p->quad_d, p->ws_d, layer_status);
+  const int weak = use_weak(*p) ? 1 : 0, skip = weak ? kGemmSkipWeak : 0;
+  k_legendre<<<ni, kLegThreads, 0, s>>>(p->items_d, p->layers_d, p->quad_d, p->ws_d, layer_status, weak);
   mark();
   const int at = (mN + 15) / 16;
   k_assemble<<<dim3(at, at, ni), 256, 0, s>>>(p->items_d, p->layers_d, p->quad_d, omega, coef, p->ws_d, layer_status);
@@ -597,47 +632,57 @@ void enqueue_solve(const LaunchSet& ls, const double* tau, const double* omega, 
   const dim3 gg(gt, gt, ni);
   k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufF, kBufE, kBufG, 0, layer_status);  // G = F~ E~
   mark();
+  // the weakly coupled orders by their own iteration; everything up to the mode vectors then skips them
+  if (weak) {
+    const int panels = weak_panels_for(*p);
+    k_weak_eigen<<<xcd_grid(ni, panels), kWeakThreads, 0, s>>>(p->items_d, ni, panels, p->ws_d, layer_status);
+  }
   // problems above the LDS size by their own kernel (the same for every schedule, so a schedule
   // never changes a result), largest first; then the others in the chosen schedule
   const int nb = p->n_big;
   if (nb > 0)
-    k_eigen_big<<<nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d);
+    k_eigen_big<<<nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d, weak);
   if (p->eigen_mode == kEigenPersistent && p->queue_d && p->order_d) {
     if (ni > nb) {
       k_reset_counter<<<1, 1, 0, s>>>(p->queue_d);
       k_eigen_persistent<<<std::min(ni - nb, p->persist_groups), kEigenThreads, 0, s>>>(
-          p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb, p->queue_d, ni - nb);
+          p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb, p->queue_d, ni - nb, weak);
     }
   } else if (p->eigen_mode == kEigenPlanOrder || !p->order_d) {
-    if (ni > nb) k_eigen<<<ni, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, nullptr);
+    if (ni > nb)
+      k_eigen<<<ni, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_plan_d, weak);
   } else if (ni > nb) {
-    k_eigen<<<ni - nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb);
+    k_eigen<<<ni - nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb,
+                                              weak);
   }
   mark();
-  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufZ, kBufX, kBufG, kGemmTransA, layer_status);  // U' = Z X
+  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufZ, kBufX, kBufG, kGemmTransA | skip,
+                             layer_status);  // U' = Z X
   mark();
   const int hqt = (std::min(mn, kHqMfmaMaxN) + 15) / 16;
-  k_hqapply_mfma<<<xcd_grid(ni, hqt), 64, 0, s>>>(p->items_d, ni, hqt, p->ws_d, layer_status);  // U = Q U'
+  k_hqapply_mfma<<<xcd_grid(ni, hqt), 64, 0, s>>>(p->items_d, ni, hqt, p->ws_d, layer_status, weak);  // U = Q U'
   if (mn > kHqMfmaMaxN) {
     const int hqb = (mn + kHqCols - 1) / kHqCols;
-    k_hqapply<<<xcd_grid(ni, hqb), 64, 0, s>>>(p->items_d, ni, hqb, p->ws_d, layer_status);
+    k_hqapply<<<xcd_grid(ni, hqb), 64, 0, s>>>(p->items_d, ni, hqb, p->ws_d, layer_status, weak);
   }
   mark();
   // one Newton step on the eigen-decomposition with the factored product F~ (E~ U)
   const int et = (mn + 15) / 16;
   const int tt = (mn + 31) / 32;
-  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufE, kBufU, kBufG, 0, layer_status);  // E~ U
-  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufF, kBufG, kBufZ, kGemmTransC, layer_status);  // (F~ E~ U)^T
-  k_transpose<<<dim3(tt, tt, ni), 256, 0, s>>>(p->items_d, p->ws_d, kBufU, kBufX, layer_status);  // U^T
-  launch_lu(dim3(ni, 1), s, p->items_d, p->ws_d, layer_status, p->max_n, LuBufs{{kBufX, kBufX}, {kBufYS, kBufYS}});
+  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufE, kBufU, kBufG, skip, layer_status);  // E~ U
+  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufF, kBufG, kBufZ, kGemmTransC | skip,
+                             layer_status);  // (F~ E~ U)^T
+  k_transpose<<<dim3(tt, tt, ni), 256, 0, s>>>(p->items_d, p->ws_d, kBufU, kBufX, layer_status, weak);  // U^T
+  launch_lu(dim3(ni, 1), s, p->items_d, p->ws_d, layer_status, p->max_n,
+            LuBufs{{kBufX, kBufX}, {kBufYS, kBufYS}, 0, weak});
   launch_trsm(p->trsm_rows, dim3(xcd_grid(ni, p->trsm_tiles)), p->trsm_lds, s, p->items_d, ni, p->trsm_tiles,
-              p->ws_d, layer_status, TrsmBufs{{kBufYS, kBufYS}, {kBufZ, kBufZ}, {kBufG, kBufG}, 1, 0});  // Y^T = (G U)^T U^-T
-  k_refine_lam<<<dim3((mn + 255) / 256, ni), 256, 0, s>>>(p->items_d, p->ws_d, layer_status);
-  k_refine_close<<<dim3(et, et, ni), dim3(16, 16), 0, s>>>(p->items_d, p->ws_d, layer_status);
-  k_refine_pairs<<<dim3((mn + 255) / 256, ni), 256, 0, s>>>(p->items_d, p->ws_d, layer_status);
-  k_refine_delta<<<dim3(et, et, ni), dim3(16, 16), 0, s>>>(p->items_d, p->ws_d, layer_status);
-  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufU, kBufX, kBufZ, 0, layer_status);  // U (I + X) Q
-  k_refine_commit<<<dim3((mn * mn + 255) / 256, ni), 256, 0, s>>>(p->items_d, p->ws_d, layer_status);
+              p->ws_d, layer_status, TrsmBufs{{kBufYS, kBufYS}, {kBufZ, kBufZ}, {kBufG, kBufG}, 1, 0, weak});  // Y^T = (G U)^T U^-T
+  k_refine_lam<<<dim3((mn + 255) / 256, ni), 256, 0, s>>>(p->items_d, p->ws_d, layer_status, weak);
+  k_refine_close<<<dim3(et, et, ni), dim3(16, 16), 0, s>>>(p->items_d, p->ws_d, layer_status, weak);
+  k_refine_pairs<<<dim3((mn + 255) / 256, ni), 256, 0, s>>>(p->items_d, p->ws_d, layer_status, weak);
+  k_refine_delta<<<dim3(et, et, ni), dim3(16, 16), 0, s>>>(p->items_d, p->ws_d, layer_status, weak);
+  k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufU, kBufX, kBufZ, skip, layer_status);  // U (I + X) Q
+  k_refine_commit<<<dim3((mn * mn + 255) / 256, ni), 256, 0, s>>>(p->items_d, p->ws_d, layer_status, weak);
   if (beams) enqueue_beam_particular(*p, omega, coef, layer_status, s);  // needs F~, before the boundary solve
   mark();
   k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufE, kBufU, kBufG, 0, layer_status);  // V = E~ U

@@ -81,14 +81,16 @@ __device__ inline double wseq_value(WSeq& q, int l, double x) {
 // The three recurrences d_{m0}, d_{m2}, d_{m,-2} of a node run on three threads (thread =
 // 128 sequence + node, N <= 128): each writes its own slot, d_{m2} and d_{m,-2} into the R and T
 // slots, and after a barrier R = -(d_{m2} + d_{m,-2})/2 and T = -(d_{m2} - d_{m,-2})/2 are formed
-// in place. Launched with kLegThreads threads.
+// in place. Launched with kLegThreads threads. Also sets the order's mark for the iteration of
+// weakly coupled orders (weak: whether the solve runs it).
 __global__ __launch_bounds__(kLegThreads) void k_legendre(const Item* items, const Layer* layers,
                                                           const double* quad, double* ws,
-                                                          const int32_t* status) {
+                                                          const int32_t* status, int weak) {
   const Item it = items[blockIdx.x];
   if (status[it.layer] != 0) return;
   const Layer ly = layers[it.layer];
   const int N = it.N, L = it.L, m = it.m;
+  if (threadIdx.x == 0) *weak_flag(ws + it.ws + extras_off(it.n), it.n) = weak ? -1 : 0;
   double* leg = ws + it.ws + leg_off(it.n);
   const int seq = threadIdx.x / 128, i = threadIdx.x % 128;
   if (i < N) {

@@ -385,6 +385,7 @@ __global__ __launch_bounds__(kLuThreadsLds) void k_lu(const Item* items, double*
   const Item it = items[blockIdx.x];
   if (status[it.layer] != 0) return;
   if ((it.n > kLdsMaxn) != ((int)blockDim.x == kLuThreadsBig)) return;  // the other launch's systems
+  if (weak_done(b.skip_weak, ws, it)) return;
   const int n = it.n, tid = threadIdx.x, NT = blockDim.x;
   const int which = blockIdx.y;
   double* base = ws + it.ws;
@@ -686,7 +687,7 @@ __global__ __launch_bounds__(64) void k_trsm(const Item* items, int n_items, int
   const Item it = items[g / b.sides];
   if (status[it.layer] != 0) return;
   const int r0 = tile * kRows;
-  if (r0 >= it.n) return;
+  if (r0 >= it.n || weak_done(b.skip_weak, ws, it)) return;
   const int side = g % b.sides;
   const int n = it.n;
   double* base = ws + it.ws;

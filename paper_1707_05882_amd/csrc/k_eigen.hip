@@ -2096,9 +2096,9 @@ __device__ __forceinline__ void eigen_body(const Item& it, double* base, int32_t
 // One workgroup per problem of at most kLdsMaxn rows: workgroup b solves items[order[b]] (order
 // null: items[b]); larger problems are left to k_eigen_big.
 __global__ __launch_bounds__(kEigenThreads) void k_eigen(const Item* items, double* ws, int32_t* status,
-                                                          int sweep_cap, const int32_t* order) {
+                                                          int sweep_cap, const int32_t* order, int weak) {
   const Item it = items[order ? order[blockIdx.x] : blockIdx.x];
-  if (status[it.layer] != 0 || it.n > kLdsMaxn) return;
+  if (status[it.layer] != 0 || it.n > kLdsMaxn || weak_done(weak, ws, it)) return;
   __shared__ double sH[kLdsMaxn * (kLdsMaxn + 1) + 3 * 64];
   __shared__ double srefl[2 * 3 * kMaxn];
   __shared__ double sred[16];
@@ -2110,11 +2110,12 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen(const Item* items, doub
 
 // Problems larger than kLdsMaxn (H and Z in global memory, multi-bulge passes through an LDS
 // window): workgroup b solves items[order[b]] (order null: items[b]). A kernel of its own so that
-// its register allocation does not weigh on the LDS-resident path.
+// its register allocation does not weigh on the LDS-resident path (one kernel for both forms made
+// the LDS form 3% slower).
 __global__ __launch_bounds__(kEigenThreads) void k_eigen_big(const Item* items, double* ws, int32_t* status,
-                                                              int sweep_cap, const int32_t* order) {
+                                                              int sweep_cap, const int32_t* order, int weak) {
   const Item it = items[order ? order[blockIdx.x] : blockIdx.x];
-  if (status[it.layer] != 0 || it.n <= kLdsMaxn) return;
+  if (status[it.layer] != 0 || it.n <= kLdsMaxn || weak_done(weak, ws, it)) return;
   __shared__ double sbuf[kWin * kWinLd + kWin * kWinU];
   __shared__ double srefl[2 * 3 * kMaxn];
   __shared__ double sred[16];
@@ -2129,7 +2130,7 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen_big(const Item* items, 
 // reaches the exit once the counter passes n_items.
 __global__ __launch_bounds__(kEigenThreads) void k_eigen_persistent(const Item* items, double* ws, int32_t* status,
                                                                      int sweep_cap, const int32_t* order,
-                                                                     int32_t* queue, int n_items) {
+                                                                     int32_t* queue, int n_items, int weak) {
   __shared__ double sH[kLdsMaxn * (kLdsMaxn + 1) + 3 * 64];
   __shared__ double srefl[2 * 3 * kMaxn];
   __shared__ double sred[16];
@@ -2144,7 +2145,7 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen_persistent(const Item* 
     const int pos = snext;
     if (pos >= n_items) return;
     const Item it = items[order[pos]];
-    if (status[it.layer] != 0 || it.n > kLdsMaxn) continue;
+    if (status[it.layer] != 0 || it.n > kLdsMaxn || weak_done(weak, ws, it)) continue;
     eigen_body<true>(it, ws + it.ws, status, sH, srefl, sred, sctl, sxyz, zops, sweep_cap);
   }
 }
@@ -2243,12 +2244,12 @@ __device__ __forceinline__ void hqapply_body(const Item& it, int tile, double* w
 constexpr int kHqLd = 17;
 
 __global__ __launch_bounds__(64) void k_hqapply_mfma(const Item* items, int n_items, int tiles, double* ws,
-                                                      const int32_t* status) {
+                                                      const int32_t* status, int weak) {
   int g, tile;
   xcd_split(blockIdx.x, tiles, g, tile);  // the column blocks of one item share an XCD
   if (g >= n_items) return;
   const Item it = items[g];
-  if (status[it.layer] != 0 || it.n > kHqMfmaMaxN) return;
+  if (status[it.layer] != 0 || it.n > kHqMfmaMaxN || weak_done(weak, ws, it)) return;
   const int n = it.n, c0 = tile * 16;
   if (c0 >= n) return;
   double* base = ws + it.ws;
@@ -2340,12 +2341,12 @@ __global__ __launch_bounds__(64) void k_hqapply_mfma(const Item* items, int n_it
 }
 
 __global__ __launch_bounds__(64) void k_hqapply(const Item* items, int n_items, int tiles, double* ws,
-                                                 const int32_t* status) {
+                                                 const int32_t* status, int weak) {
   int g, tile;
   xcd_split(blockIdx.x, tiles, g, tile);  // the column blocks of one item share an XCD
   if (g >= n_items) return;
   const Item it = items[g];
-  if (status[it.layer] != 0 || it.n <= kHqMfmaMaxN) return;
+  if (status[it.layer] != 0 || it.n <= kHqMfmaMaxN || weak_done(weak, ws, it)) return;
   __shared__ double sb[kMaxn * kHqCols];  // rows x kHqCols columns
   __shared__ double stau[kMaxn];          // tau_k of every reflector
   if (it.n <= 128)

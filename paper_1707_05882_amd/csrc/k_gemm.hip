@@ -52,6 +52,7 @@ __global__ __launch_bounds__(256) void k_gemm(const Item* items, double* ws, int
   const int n = it.n;
   const int r0 = (tile / gridDim.x) * kGT, c0 = (tile % gridDim.x) * kGT;
   if (r0 >= n || c0 >= n) return;
+  if (weak_done(mode & kGemmSkipWeak, ws, it)) return;
   const double* A = buf_ptr(ws, it, bufA);
   const double* B = buf_ptr(ws, it, bufB);
   double* C = buf_ptr(ws, it, bufC);

@@ -31,9 +31,9 @@ constexpr double kRefineMaxCorr = 0.1;
 
 // dst = src^T for every item, 32 x 32 tiles through LDS (both sides coalesced).
 __global__ __launch_bounds__(256) void k_transpose(const Item* items, double* ws, int src, int dst,
-                                                   const int32_t* status) {
+                                                   const int32_t* status, int skip_weak) {
   const Item it = items[blockIdx.z];
-  if (status[it.layer] != 0) return;
+  if (status[it.layer] != 0 || weak_done(skip_weak, ws, it)) return;
   const int n = it.n;
   const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
   if (r0 >= n || c0 >= n) return;
@@ -68,9 +68,9 @@ __device__ inline RefineCols refine_cols(double* ex, int n) {
 
 // Per column j: the new eigenvalue (1x1: Y_jj; pair: the standard form of its 2x2 block of Y), the
 // column's entries of Q, and a zero close-partner count.
-__global__ __launch_bounds__(256) void k_refine_lam(const Item* items, double* ws, const int32_t* status) {
+__global__ __launch_bounds__(256) void k_refine_lam(const Item* items, double* ws, const int32_t* status, int weak) {
   const Item it = items[blockIdx.y];
-  if (status[it.layer] != 0) return;
+  if (status[it.layer] != 0 || weak_done(weak, ws, it)) return;
   const int n = it.n;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
@@ -201,9 +201,9 @@ __device__ inline double corr_entry(const double* YT, int n, const double* lre, 
 
 // Close block pairs: one thread per (row block leader, column block leader) counts the column
 // block's close partners of row block a, and records the last one.
-__global__ void k_refine_close(const Item* items, double* ws, const int32_t* status) {
+__global__ void k_refine_close(const Item* items, double* ws, const int32_t* status, int weak) {
   const Item it = items[blockIdx.z];
-  if (status[it.layer] != 0) return;
+  if (status[it.layer] != 0 || weak_done(weak, ws, it)) return;
   const int n = it.n;
   const int i = blockIdx.y * 16 + threadIdx.y;
   const int k = blockIdx.x * 16 + threadIdx.x;
@@ -224,9 +224,9 @@ __global__ void k_refine_close(const Item* items, double* ws, const int32_t* sta
 
 // A close pair of real eigenvalues a, b, each close to nothing else: the eigenvectors of the 2 x 2
 // block C = Y[{a, b}, {a, b}] (real eigenvalues; a pair that turned complex is left as it was).
-__global__ __launch_bounds__(256) void k_refine_pairs(const Item* items, double* ws, const int32_t* status) {
+__global__ __launch_bounds__(256) void k_refine_pairs(const Item* items, double* ws, const int32_t* status, int weak) {
   const Item it = items[blockIdx.y];
-  if (status[it.layer] != 0) return;
+  if (status[it.layer] != 0 || weak_done(weak, ws, it)) return;
   const int n = it.n;
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= n) return;
@@ -265,9 +265,9 @@ __global__ __launch_bounds__(256) void k_refine_pairs(const Item* items, double*
 }
 
 // M = (I + X) Q entry by entry, into kBufX.
-__global__ void k_refine_delta(const Item* items, double* ws, const int32_t* status) {
+__global__ void k_refine_delta(const Item* items, double* ws, const int32_t* status, int weak) {
   const Item it = items[blockIdx.z];
-  if (status[it.layer] != 0) return;
+  if (status[it.layer] != 0 || weak_done(weak, ws, it)) return;
   const int n = it.n;
   const int i = blockIdx.y * 16 + threadIdx.y;
   const int j = blockIdx.x * 16 + threadIdx.x;
@@ -287,9 +287,9 @@ __global__ void k_refine_delta(const Item* items, double* ws, const int32_t* sta
 }
 
 // U <- U M (computed into kBufZ by the GEMM before this kernel), eigenvalues <- the new ones.
-__global__ __launch_bounds__(256) void k_refine_commit(const Item* items, double* ws, const int32_t* status) {
+__global__ __launch_bounds__(256) void k_refine_commit(const Item* items, double* ws, const int32_t* status, int weak) {
   const Item it = items[blockIdx.y];
-  if (status[it.layer] != 0) return;
+  if (status[it.layer] != 0 || weak_done(weak, ws, it)) return;
   const int n = it.n;
   double* base = ws + it.ws;
   const double* Z = base + (int64_t)kBufZ * n * n;

@@ -90,6 +90,15 @@ __host__ __device__ inline int64_t block_doubles_beams(int n, int N, int L, int 
 }
 constexpr int kMaxBeams = 64;  // incident directions per plan
 
+// Per-order mark of the iteration for weakly coupled orders (k_weak.hip), in the second pivot slot of
+// the extras block, which is free until the boundary factorisation: negative while the order is solved
+// by that iteration (k_legendre sets it), 0 once it has been given up. A pivot is never negative.
+__host__ __device__ inline int* weak_flag(double* ex, int n) { return reinterpret_cast<int*>(ex + 2 * (int64_t)n) + n; }
+// weak: whether the solve ran that iteration (otherwise the mark is not read)
+__device__ inline bool weak_done(int weak, double* ws, const Item& it) {
+  return weak && *weak_flag(ws + it.ws + extras_off(it.n), it.n) < 0;
+}
+
 struct BeamTask {  // one workgroup of the beam synthesis: (layer, outgoing node i, incident mu0_j)
   int32_t layer, i, j, pad;
 };
@@ -111,13 +120,25 @@ __global__ void k_validate(const Layer* layers, int n_layers, const double* tau,
                            const double* coef, int32_t* status);
 constexpr int kLegThreads = 3 * 128;  // k_legendre: three recurrences x up to 128 nodes
 __global__ void k_legendre(const Item* items, const Layer* layers, const double* quad, double* ws,
-                           const int32_t* status);
+                           const int32_t* status, int weak);
 __global__ void k_assemble(const Item* items, const Layer* layers, const double* quad, const double* omega,
                            const double* coef, double* ws, const int32_t* status);
 // C = op(A) op(B) for buffers of one item; mode: OR of the bits below (C written transposed,
 // negated, or added to the existing C)
-constexpr int kGemmTransA = 1, kGemmTransB = 2, kGemmTransC = 4, kGemmNegate = 8, kGemmAccumulate = 16;
+// (kGemmSkipWeak: not for the orders that k_weak_eigen has solved)
+constexpr int kGemmTransA = 1, kGemmTransB = 2, kGemmTransC = 4, kGemmNegate = 8, kGemmAccumulate = 16,
+              kGemmSkipWeak = 32;
 __global__ void k_gemm(const Item* items, double* ws, int bufA, int bufB, int bufC, int mode, const int32_t* status);
+// Eigen-decomposition of the weakly coupled orders (k_weak.hip); the eigensolver proper, its
+// back-transformation and the refinement leave out the orders that it has solved.
+constexpr int kWeakThreads = 512;
+__host__ __device__ inline int weak_cols(int n) { return n <= 128 ? 64 : (n <= 256 ? 32 : 16); }  // per panel
+__host__ __device__ inline int weak_panels(int n) { return (n + weak_cols(n) - 1) / weak_cols(n); }
+constexpr int kWeakAllMaxN = 128;  // above it k_weak_eigen takes the faint orders only
+// orders per solve above which the iteration is run: the compute units, each of which holds one problem
+// of the general eigensolver
+constexpr int kWeakAboveItems = 256;
+__global__ void k_weak_eigen(const Item* items, int n_items, int panels, double* ws, const int32_t* status);
 // sweep_cap: largest number of QR sweeps per problem (above it the layer is NUMERIC), 0 = default.
 // order: item permutation (workgroup b solves items[order[b]]), or null for the plan order. The
 // persistent form takes positions of `order` from the counter `queue` (reset to 0 before the
@@ -125,11 +146,12 @@ __global__ void k_gemm(const Item* items, double* ws, int bufA, int bufB, int bu
 constexpr int kEigenPlanOrder = 0, kEigenLongestFirst = 1, kEigenPersistent = 2;
 // k_eigen and k_eigen_persistent solve the problems of at most kLdsMaxn rows (H in LDS);
 // k_eigen_big the larger ones, over the first n_big positions of the longest-first order (which
-// are exactly those), whatever the schedule.
-__global__ void k_eigen(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order);
-__global__ void k_eigen_big(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order);
+// are exactly those), whatever the schedule. weak: leave out the orders that k_weak_eigen has solved.
+__global__ void k_eigen(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order, int weak);
+__global__ void k_eigen_big(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order,
+                            int weak);
 __global__ void k_eigen_persistent(const Item* items, double* ws, int32_t* status, int sweep_cap,
-                                   const int32_t* order, int32_t* queue, int n_items);
+                                   const int32_t* order, int32_t* queue, int n_items, int weak);
 __global__ void k_reset_counter(int32_t* counter);
 __global__ void k_vfix(const Item* items, double* ws, int32_t* status);
 __global__ void k_colscal(const Item* items, const double* tau, double* ws, int32_t* status);
@@ -138,8 +160,9 @@ constexpr int kHqCols = 4;  // columns per k_hqapply wave
 // k_hqapply_mfma (16 columns per wave, panels of 16 reflectors on the matrix cores) takes the
 // systems of at most kHqMfmaMaxN rows, k_hqapply the larger ones
 constexpr int kHqMfmaMaxN = 256;
-__global__ void k_hqapply(const Item* items, int n_items, int tiles, double* ws, const int32_t* status);
-__global__ void k_hqapply_mfma(const Item* items, int n_items, int tiles, double* ws, const int32_t* status);
+__global__ void k_hqapply(const Item* items, int n_items, int tiles, double* ws, const int32_t* status, int weak);
+__global__ void k_hqapply_mfma(const Item* items, int n_items, int tiles, double* ws, const int32_t* status,
+                               int weak);
 // Buffers of the factorisation and right-division kernels per side (blockIdx.y of k_lu, or the
 // low digit of the matrix index of k_trsm): LU of src into the transposed factor dst; right
 // division y = rhs a^-1 with a's factor in buffer a. The side also selects the pivot and 1 / Uu_kk
@@ -147,11 +170,13 @@ __global__ void k_hqapply_mfma(const Item* items, int n_items, int tiles, double
 struct LuBufs {
   int32_t src[2], dst[2];
   int32_t only_flagged;  // factor only the sides whose FP32 refinement asked for the FP64 solve
+  int32_t skip_weak;     // not the orders that k_weak_eigen has solved
 };
 struct TrsmBufs {
   int32_t a[2], rhs[2], y[2];
   int32_t sides;         // 1 or 2 matrices per item
   int32_t only_flagged;  // as in LuBufs
+  int32_t skip_weak;     // as in LuBufs
 };
 
 // State of the FP32-refined boundary solve per item, in the extras block at [3n, 3n + 4) (free
@@ -190,12 +215,13 @@ void launch_trsm(int rows, dim3 grid, size_t lds, hipStream_t s, const Item* ite
 const void* trsm_kernel_ptr(int rows);
 // Eigenpair refinement of the homogeneous step (between the eigenvector back-transformation and the
 // mode vectors): transposed copy, per-column update of the eigenvalues, correction matrix, commit.
-__global__ void k_transpose(const Item* items, double* ws, int src, int dst, const int32_t* status);
-__global__ void k_refine_lam(const Item* items, double* ws, const int32_t* status);
-__global__ void k_refine_close(const Item* items, double* ws, const int32_t* status);
-__global__ void k_refine_pairs(const Item* items, double* ws, const int32_t* status);
-__global__ void k_refine_delta(const Item* items, double* ws, const int32_t* status);
-__global__ void k_refine_commit(const Item* items, double* ws, const int32_t* status);
+__global__ void k_transpose(const Item* items, double* ws, int src, int dst, const int32_t* status,
+                            int skip_weak = 0);
+__global__ void k_refine_lam(const Item* items, double* ws, const int32_t* status, int weak);
+__global__ void k_refine_close(const Item* items, double* ws, const int32_t* status, int weak);
+__global__ void k_refine_pairs(const Item* items, double* ws, const int32_t* status, int weak);
+__global__ void k_refine_delta(const Item* items, double* ws, const int32_t* status, int weak);
+__global__ void k_refine_commit(const Item* items, double* ws, const int32_t* status, int weak);
 // right-hand-side rows per right-division tile (one wave, 64 / kTrsmRows lanes per row; the tile takes
 // n x (trsm_ldb(n) + 2) doubles of LDS). The FP32 right division and the allocation-free entry point
 // use this shape; plans start from kTrsmRowsDefault, the 16-row tile whose products run on the
@@ -271,7 +297,8 @@ struct LaunchSet {
   size_t trsm_lds = 0;        // its LDS bytes
   int trsm32_tiles = 0;       // row tiles of the FP32 right division (kTrsmRows rows each)
   int eigen_mode = 0;         // k_eigen scheduling: kEigenPlanOrder / kEigenLongestFirst / kEigenPersistent
-  const int32_t* order_d = nullptr;  // items by decreasing size (longest first)
+  const int32_t* order_d = nullptr;       // items longest first, those with n > kLdsMaxn in front
+  const int32_t* order_plan_d = nullptr;  // items in plan order, the low orders first (null: plan order)
   int32_t* queue_d = nullptr;        // work counter of the persistent eigensolver
   int persist_groups = 256;          // workgroups of the persistent eigensolver (compute units)
   int n_big = 0;                     // items with n > kLdsMaxn (the first n_big positions of order_d)
