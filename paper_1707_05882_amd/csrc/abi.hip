@@ -110,6 +110,18 @@ vbrdf_status upload(const std::vector<T>& h, T** d) {
   return VBRDF_OK;
 }
 
+// Whether the solve runs the iteration for weakly coupled orders first. It frees compute units, so it
+// pays where the general eigensolver would need more than one round of them (one problem per unit),
+// or where its problems contend for the memory (n > 256: 256 orders at n = 512 took 851 ms, with the
+// 10 strongly coupled ones left to it 443 ms); below that the strongly coupled orders bound the stage
+// either way and the iteration only delays them (64 orders at n = 128: 4.56 against 4.83 ms). Not with
+// a cap on the QR sweeps (a forced failure, which needs every order to go by the QR), and not where
+// the adjoint's state is kept: its gradients amplify the rounding of the eigenvectors of weak orders
+// (dF / d coefficient of the highest degrees is good to 1e-5 at N = 44), so they keep their rounding.
+static bool use_weak(const LaunchSet& ls) {
+  return ls.qr_sweep_cap == 0 && !ls.save && (ls.n_items > kWeakAboveItems || ls.max_n > 256);
+}
+
 }  // namespace
 
 struct vbrdf_plan : LaunchSet {
@@ -407,6 +419,8 @@ vbrdf_status vbrdf_plan_create(const vbrdf_plan_desc* d, vbrdf_plan** out) {
     p->layers_h.push_back(ly);
   }
   p->n_items = (int)p->items_h.size();
+  p->qr_sweep_cap = d->qr_sweep_cap;
+  p->save = (d->flags & VBRDF_FLAG_SAVE_FOR_BACKWARD) != 0;
   p->n_tasks = (int)tasks.size();
   p->out_doubles = (size_t)out_off;
   p->ws_bytes = (size_t)ws_off * sizeof(double);
@@ -436,21 +450,25 @@ vbrdf_status vbrdf_plan_create(const vbrdf_plan_desc* d, vbrdf_plan** out) {
   if (st == VBRDF_OK) st = upload(quad, &quad_d);
   p->quad_d = quad_d;
   if (st == VBRDF_OK) {
-    // Eigensolver work orders. The low orders are the ones that the iteration for weakly coupled orders
-    // leaves (those below 16 hold all of them up to asymmetries of 0.9): they come first, so that they
-    // start at once and spread over the XCDs (in plain plan order the like orders of layers with 8 k
-    // orders fell on the same XCDs, 32 against 8 ms for 72 layers of 64 orders at N = 32).
+    // Eigensolver work order: largest systems first (stable). Where the iteration for weakly coupled orders
+    // runs, the low orders are the ones that it leaves (those below 16 hold all of them up to
+    // asymmetries of 0.9): they come first, so that they start at once and spread over the XCDs (in plain
+    // plan order the like orders of layers with 8 k orders fell on the same XCDs, 32 against 8 ms for 72
+    // layers of 64 orders at N = 32).
+    const bool weak = use_weak(*p);
     std::vector<int32_t> order(p->items_h.size());
     for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
     auto low = [&](int32_t i) { return p->items_h[i].m < 16; };
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return low(a) > low(b); });
-    int32_t* plan_d = nullptr;
-    st = upload(order, &plan_d);
-    p->order_plan_d = plan_d;
+    if (weak) {
+      std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return low(a) > low(b); });
+      int32_t* plan_d = nullptr;
+      st = upload(order, &plan_d);
+      p->order_plan_d = plan_d;
+    }
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
       const int na = p->items_h[a].n, nb = p->items_h[b].n;
       if ((na > kLdsMaxn) != (nb > kLdsMaxn)) return na > kLdsMaxn;
-      return low(a) != low(b) ? low(a) : na > nb;
+      return weak && low(a) != low(b) ? low(a) : na > nb;
     });
     for (const Item& it : p->items_h) p->n_big += it.n > kLdsMaxn ? 1 : 0;
     int32_t* order_d = nullptr;
@@ -475,10 +493,8 @@ vbrdf_status vbrdf_plan_create(const vbrdf_plan_desc* d, vbrdf_plan** out) {
   p->graph = (d->flags & VBRDF_FLAG_GRAPH) != 0;
   p->precision = d->precision;
   p->transmission = (d->flags & VBRDF_FLAG_EMIT_TRANSMISSION) != 0;
-  p->qr_sweep_cap = d->qr_sweep_cap;
   p->no_fallback = (d->flags & VBRDF_FLAG_DISABLE_FP64_FALLBACK) != 0;
   p->refine_steps = d->refine_steps == 0 ? kBoundaryRefineSteps : (d->refine_steps < 0 ? 0 : d->refine_steps);
-  p->save = (d->flags & VBRDF_FLAG_SAVE_FOR_BACKWARD) != 0;
   if (p->save) {
     for (const Layer& ly : p->layers_h)
       if (6 * (int64_t)ly.L > 16 * (int64_t)ly.N * ly.N) {
@@ -580,18 +596,6 @@ namespace vbrdf {
 
 static void enqueue_stacks(const LaunchSet& ls, const double* base, int32_t* layer_status, hipStream_t s);
 
-// Whether the solve runs the iteration for weakly coupled orders first. It frees compute units, so it
-// pays where the general eigensolver would need more than one round of them (one problem per unit),
-// or where its problems contend for the memory (n > 256: 256 orders at n = 512 took 851 ms, with the
-// 10 strongly coupled ones left to it 443 ms); below that the strongly coupled orders bound the stage
-// either way and the iteration only delays them (64 orders at n = 128: 4.56 against 4.83 ms). Not with
-// a cap on the QR sweeps (a forced failure, which needs every order to go by the QR), and not where
-// the adjoint's state is kept: its gradients amplify the rounding of the eigenvectors of weak orders
-// (dF / d coefficient of the highest degrees is good to 1e-5 at N = 44), so they keep their rounding.
-static bool use_weak(const LaunchSet& ls) {
-  return ls.qr_sweep_cap == 0 && !ls.save && (ls.n_items > kWeakAboveItems || ls.max_n > 256);
-}
-
 // Panels of k_weak_eigen for the largest item. Sizes up to 256 use their widest panels below it too
 // (64 columns up to n = 128, 32 up to 256), so the largest number can be that of a smaller size.
 static int weak_panels_for(const LaunchSet& ls) {
@@ -642,18 +646,19 @@ void enqueue_solve(const LaunchSet& ls, const double* tau, const double* omega, 
   const int nb = p->n_big;
   if (nb > 0)
     k_eigen_big<<<nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d, weak);
+  const auto eigen = p->save ? &k_eigen : &k_eigen_lds;
+  const auto eigen_persistent = p->save ? &k_eigen_persistent : &k_eigen_lds_persistent;
   if (p->eigen_mode == kEigenPersistent && p->queue_d && p->order_d) {
     if (ni > nb) {
       k_reset_counter<<<1, 1, 0, s>>>(p->queue_d);
-      k_eigen_persistent<<<std::min(ni - nb, p->persist_groups), kEigenThreads, 0, s>>>(
+      eigen_persistent<<<std::min(ni - nb, p->persist_groups), kEigenThreads, 0, s>>>(
           p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb, p->queue_d, ni - nb, weak);
     }
   } else if (p->eigen_mode == kEigenPlanOrder || !p->order_d) {
     if (ni > nb)
-      k_eigen<<<ni, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_plan_d, weak);
+      eigen<<<ni, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_plan_d, weak);
   } else if (ni > nb) {
-    k_eigen<<<ni - nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb,
-                                              weak);
+    eigen<<<ni - nb, kEigenThreads, 0, s>>>(p->items_d, p->ws_d, layer_status, p->qr_sweep_cap, p->order_d + nb, weak);
   }
   mark();
   k_gemm<<<gg, 256, 0, s>>>(p->items_d, p->ws_d, kBufZ, kBufX, kBufG, kGemmTransA | skip,

@@ -144,14 +144,22 @@ __global__ void k_weak_eigen(const Item* items, int n_items, int panels, double*
 // persistent form takes positions of `order` from the counter `queue` (reset to 0 before the
 // launch) until n_items are taken.
 constexpr int kEigenPlanOrder = 0, kEigenLongestFirst = 1, kEigenPersistent = 2;
-// k_eigen and k_eigen_persistent solve the problems of at most kLdsMaxn rows (H in LDS);
-// k_eigen_big the larger ones, over the first n_big positions of the longest-first order (which
-// are exactly those), whatever the schedule. weak: leave out the orders that k_weak_eigen has solved.
-__global__ void k_eigen(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order, int weak);
+// k_eigen_lds and k_eigen_lds_persistent (k_eigen_lds.hip) solve the problems of at most kLdsMaxn rows,
+// k_eigen_big the larger ones, over the first n_big positions of the longest-first order (which are
+// exactly those), whatever the schedule. Plans that keep the adjoint's state take k_eigen and
+// k_eigen_persistent for the former: its gradients amplify the rounding of the eigenvectors of weakly
+// coupled orders (dF / d coefficient of the highest degrees is good to 1e-5 at N = 44), so they stay with
+// the kernel whose rounding they had. weak: leave out the orders that k_weak_eigen has solved
+// (it never runs for the plans of k_eigen and k_eigen_persistent, which have the parameter for the launch alone).
+__global__ void k_eigen_lds(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order,
+                            int weak);
+__global__ void k_eigen_lds_persistent(const Item* items, double* ws, int32_t* status, int sweep_cap,
+                                       const int32_t* order, int32_t* queue, int n_items, int weak);
+__global__ void k_eigen(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order, int);
 __global__ void k_eigen_big(const Item* items, double* ws, int32_t* status, int sweep_cap, const int32_t* order,
                             int weak);
 __global__ void k_eigen_persistent(const Item* items, double* ws, int32_t* status, int sweep_cap,
-                                   const int32_t* order, int32_t* queue, int n_items, int weak);
+                                   const int32_t* order, int32_t* queue, int n_items, int);
 __global__ void k_reset_counter(int32_t* counter);
 __global__ void k_vfix(const Item* items, double* ws, int32_t* status);
 __global__ void k_colscal(const Item* items, const double* tau, double* ws, int32_t* status);
