@@ -364,8 +364,8 @@ __device__ bool lu_blocked(double* __restrict__ A, int n, int* perm, double* inv
   return true;
 }
 
+constexpr int kLuPanel = (kMaxn + 1) * kLuNb;        // LDS panel of the blocked factorisation
 constexpr int kLuLds = kLdsMaxn * (kLdsMaxn + 1);  // LDS matrix
-static_assert(kLuLds >= (kMaxn + 1) * kLuNb, "the panel of the blocked factorisation fits");
 constexpr int kVfixLds = kLuLds + kLdsMaxn;          // LDS matrix and one work vector
 static_assert(kVfixLds >= 2 * 256, "the column-maximum partials of a 256-thread block fit");
 
@@ -376,48 +376,34 @@ __device__ inline int* lu_perm(double* ex, int n, int which) {
   return reinterpret_cast<int*>(ex + 2 * (int64_t)n) + which * n;
 }
 
-// LU factorisation with partial pivoting of buffer b.src[side] (side = blockIdx.y: S' and T' of the
-// boundary solve, or U^T of the eigenpair refinement), P^T A = L Uu. The factor is written
+// LU factorisation with partial pivoting of buffer b.src[side] (side = blockIdx.y), P^T A = L Uu, of the
+// systems of more than kLuRegMaxn rows: in place and blocked. The factor is written
 // transposed into b.dst[side], AT[j n + c] = A(c, j), so that column j of Uu (c < j) and of L
 // (c > j) are contiguous for the right division; pivots and 1 / Uu_kk go to the extras block.
-// The source buffer is overwritten when n > kLdsMaxn (factored in place, in blocked form).
-__global__ __launch_bounds__(kLuThreadsLds) void k_lu(const Item* items, double* ws, int32_t* status, LuBufs b) {
+// The source buffer is overwritten.
+__global__ __launch_bounds__(kLuThreadsBig) void k_lu(const Item* items, double* ws, int32_t* status, LuBufs b) {
   const Item it = items[blockIdx.x];
-  if (status[it.layer] != 0) return;
-  if ((it.n > kLdsMaxn) != ((int)blockDim.x == kLuThreadsBig)) return;  // the other launch's systems
-  if (weak_done(b.skip_weak, ws, it)) return;
+  if (status[it.layer] != 0 || it.n <= kLuRegMaxn || weak_done(b.skip_weak, ws, it)) return;
   const int n = it.n, tid = threadIdx.x, NT = blockDim.x;
   const int which = blockIdx.y;
   double* base = ws + it.ws;
   if (b.only_flagged && !boundary_flags(base + extras_off(n), n)->fallback[which]) return;
-  double* Ag = buf_ptr(ws, it, b.src[which]);
+  double* A = buf_ptr(ws, it, b.src[which]);
   double* AT = buf_ptr(ws, it, b.dst[which]);
   double* ex = base + extras_off(n);
-  __shared__ double smem[kLuLds];
+  __shared__ double smem[kLuPanel];
   __shared__ int perm[2 * kMaxn];
   __shared__ double invd[kMaxn];
-  __shared__ int redi[8];
   __shared__ double slu_rv[32];
   __shared__ double slu_l[kLuNb * (kLuNb + 1)];
   __shared__ int slu_ri[16];
-  const bool in_lds = n <= kLdsMaxn;
-  double* A = in_lds ? smem : Ag;
-  const int64_t ld = in_lds ? n + 1 : n;
-  bool ok;
-  if (in_lds) {
-    for (int t = tid; t < n * n; t += NT) smem[(t / n) * (n + 1) + (t % n)] = Ag[t];
-    __syncthreads();
-    ok = lu_factor<kLdsMaxn / 64>(smem, n + 1, n, perm, invd, redi);
-  } else {
-    ok = lu_blocked(Ag, n, perm, invd, smem, slu_l, slu_rv, slu_ri);
-  }
-  if (!ok) {
+  if (!lu_blocked(A, n, perm, invd, smem, slu_l, slu_rv, slu_ri)) {
     if (tid == 0) status[it.layer] = -5;
     return;
   }
   for (int t = tid; t < n * n; t += NT) {
     const int j = t / n, c = t % n;
-    AT[t] = A[(int64_t)perm[c] * ld + j];
+    AT[t] = A[(int64_t)perm[c] * n + j];
   }
   double* id = lu_invd(ex, n, which);
   int* pm = lu_perm(ex, n, which);
@@ -427,9 +413,14 @@ __global__ __launch_bounds__(kLuThreadsLds) void k_lu(const Item* items, double*
   }
 }
 
-void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t* status, int max_n, LuBufs b) {
-  k_lu<<<grid, kLuThreadsLds, 0, s>>>(items, ws, status, b);
-  if (max_n > kLdsMaxn) k_lu<<<grid, kLuThreadsBig, 0, s>>>(items, ws, status, b);
+void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t* status, int min_n, int max_n,
+               LuBufs b) {
+  if (max_n <= 64)
+    k_lu_reg<4><<<grid, 64 * 5, 0, s>>>(items, ws, status, b, 0);
+  else if (min_n <= 128)
+    k_lu_reg<8><<<grid, 64 * 9, 0, s>>>(items, ws, status, b, 0);
+  if (max_n > 128 && min_n <= kLuRegMaxn) k_lu_reg<12><<<grid, 64 * 13, 0, s>>>(items, ws, status, b, 128);
+  if (max_n > kLuRegMaxn) k_lu<<<grid, kLuThreadsBig, 0, s>>>(items, ws, status, b);
 }
 
 // Right division Y = B A^-1 with the factors of k_lu (S' and T' with B = U in the boundary solve,

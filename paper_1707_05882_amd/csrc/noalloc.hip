@@ -168,7 +168,7 @@ extern "C" vbrdf_status vbrdf_solve_noalloc(int32_t N, int32_t L, int32_t M, int
   ls.n_layers = 1;
   ls.n_items = M;
   ls.n_tasks = N * N;
-  ls.max_n = n;
+  ls.min_n = ls.max_n = n;
   ls.max_N = N;
   ls.trsm_rows = kTrsmRows;  // the tile shape its scratch sizes assume
   ls.trsm_tiles = (n + kTrsmRows - 1) / kTrsmRows;

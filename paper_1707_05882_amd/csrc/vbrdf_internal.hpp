@@ -171,7 +171,7 @@ constexpr int kHqMfmaMaxN = 256;
 __global__ void k_hqapply(const Item* items, int n_items, int tiles, double* ws, const int32_t* status, int weak);
 __global__ void k_hqapply_mfma(const Item* items, int n_items, int tiles, double* ws, const int32_t* status,
                                int weak);
-// Buffers of the factorisation and right-division kernels per side (blockIdx.y of k_lu, or the
+// Buffers of the factorisation and right-division kernels per side (blockIdx.y of k_lu and k_lu_reg, or the
 // low digit of the matrix index of k_trsm): LU of src into the transposed factor dst; right
 // division y = rhs a^-1 with a's factor in buffer a. The side also selects the pivot and 1 / Uu_kk
 // slots of the extras block.
@@ -207,13 +207,16 @@ __global__ void k_lu32(const Item* items, double* ws, int32_t* status);
 __global__ void k_trsm32(const Item* items, int n_items, int tiles, double* ws, int32_t* status, int accumulate);
 __global__ void k_resid(const Item* items, double* ws, const int32_t* status);
 __global__ void k_bcheck(const Item* items, double* ws, int32_t* status, int no_fallback);
-// k_lu runs twice per factorisation: with kLuThreadsLds threads over the systems held in LDS
-// (n <= kLdsMaxn) and with kLuThreadsBig over the larger, blocked ones (a thread per row);
-// launch_lu issues both (the second only when the plan has such systems).
-constexpr int kLuThreadsLds = 1024, kLuThreadsBig = 512;
+// LU with partial pivoting. k_lu_reg<kT> (k_lu.hip): systems of n_above < n <= 16 kT rows, kT + 1 waves;
+// k_lu: the systems of more than kLuRegMaxn rows, blocked, a thread per row. launch_lu issues those of
+// the size classes between the smallest and the largest system (min_n = 0: from the smallest).
+constexpr int kLuRegMaxn = 192, kLuThreadsBig = 512;
 static_assert(kLuThreadsBig >= kMaxn && kLuThreadsBig % 64 == 0, "a thread per row in the blocked LU");
+template <int kT>
+__global__ void k_lu_reg(const Item* items, double* ws, int32_t* status, LuBufs b, int n_above);
 __global__ void k_lu(const Item* items, double* ws, int32_t* status, LuBufs b);
-void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t* status, int max_n, LuBufs b);
+void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t* status, int min_n, int max_n,
+               LuBufs b);
 // one kernel per tile shape (rows per tile 4, 8 or 16); launch_trsm picks it
 template <int kRows>
 __global__ void k_trsm(const Item* items, int n_items, int tiles, double* ws, int32_t* status, TrsmBufs b);
@@ -299,7 +302,7 @@ struct LaunchSet {
   const double* quad_d = nullptr;  // per layer mu[N] then alpha[N]
   double* ws_d = nullptr;          // per-item workspace blocks
   int n_layers = 0, n_items = 0, n_tasks = 0;
-  int max_n = 0, max_N = 0;
+  int min_n = 0, max_n = 0, max_N = 0;
   int trsm_rows = kTrsmRowsDefault;  // right-hand-side rows per FP64 right-division tile (4, 8, 16)
   int trsm_tiles = 0;         // row tiles of the FP64 right division (largest item)
   size_t trsm_lds = 0;        // its LDS bytes
