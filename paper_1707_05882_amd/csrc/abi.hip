@@ -412,6 +412,7 @@ vbrdf_status vbrdf_plan_create(const vbrdf_plan_desc* d, vbrdf_plan** out) {
     for (int i = 0; i < ly.N; ++i)
       for (int q = 0; q < ly.N; ++q) tasks.push_back(SynthTask{l, i, q, 0});
     p->max_n = std::max(p->max_n, n);
+    p->max_M = std::max(p->max_M, ly.M);
     p->min_n = p->min_n ? std::min(p->min_n, n) : n;
     p->trsm32_tiles = std::max(p->trsm32_tiles, (n + kTrsmRows - 1) / kTrsmRows);
     p->max_N = std::max(p->max_N, ly.N);
@@ -749,9 +750,14 @@ void enqueue_solve(const LaunchSet& ls, const double* tau, const double* omega, 
 static void enqueue_stacks(const LaunchSet& ls, const double* base, int32_t* layer_status, hipStream_t s) {
   const LaunchSet* p = &ls;
   const int mn = p->max_n, gt = (mn + 63) / 64, et = (mn + 15) / 16;
-  if (p->base_kind != VBRDF_BASE_BLACK)
-    k_stack_validate<<<p->n_layers, 256, 0, s>>>(p->layers_d, p->below_d, p->base_kind, base, p->base_off_d,
-                                                  layer_status);
+  if (p->base_kind != VBRDF_BASE_BLACK) {
+    int64_t most = 1;  // entries of the largest Mueller base
+    if (p->base_kind == VBRDF_BASE_MUELLER) most = (int64_t)p->max_M * mn * mn;
+    const int64_t chunks = (most + 256 * kBaseChunk - 1) / (256 * kBaseChunk);
+    k_stack_validate<<<(unsigned)(chunks * p->n_layers), 256, 0, s>>>(p->layers_d, p->n_layers, p->below_d,
+                                                                      p->base_kind, base, p->base_off_d,
+                                                                      layer_status);
+  }
   k_stack_status<<<(p->n_layers + 255) / 256, 256, 0, s>>>(p->n_layers, p->below_d, layer_status);
   const int xb = std::min(1024, (mn * mn + 255) / 256);
   for (int k = 0; k < p->n_levels; ++k) {

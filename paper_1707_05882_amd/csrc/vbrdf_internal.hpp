@@ -234,9 +234,8 @@ __global__ void k_refine_pairs(const Item* items, double* ws, const int32_t* sta
 __global__ void k_refine_delta(const Item* items, double* ws, const int32_t* status, int weak);
 __global__ void k_refine_commit(const Item* items, double* ws, const int32_t* status, int weak);
 // right-hand-side rows per right-division tile (one wave, 64 / kTrsmRows lanes per row; the tile takes
-// n x (trsm_ldb(n) + 2) doubles of LDS). The FP32 right division and the allocation-free entry point
-// use this shape; plans start from kTrsmRowsDefault, the 16-row tile whose products run on the
-// matrix cores.
+// n x (trsm_ldb(n) + 2) doubles of LDS). The FP32 right division uses this shape; the FP64 one starts
+// from kTrsmRowsDefault, the 16-row tile whose products run on the matrix cores.
 constexpr int kTrsmRows = 8;
 constexpr int kTrsmRowsDefault = 16;
 // LDS row stride of the right-division tile, in doubles. A 64-bit LDS access is served 16 lanes
@@ -284,8 +283,9 @@ struct StackTask {
   int32_t pad;
 };
 constexpr int kMaxStackLevels = 64;
-__global__ void k_stack_validate(const Layer* layers, const int32_t* below, int base_kind, const double* base,
+__global__ void k_stack_validate(const Layer* layers, int n_layers, const int32_t* below, int base_kind, const double* base,
                                  const int64_t* base_off, int32_t* status);
+constexpr int kBaseChunk = 8;  // entries of a Mueller base that a thread of k_stack_validate looks at
 __global__ void k_stack_status(int n_layers, const int32_t* below, int32_t* status);
 __global__ void k_stack_x(const Item* items, const StackTask* tasks, const Layer* layers, const double* quad,
                           int base_kind, const double* base, double* ws, int32_t* status);
@@ -302,7 +302,7 @@ struct LaunchSet {
   const double* quad_d = nullptr;  // per layer mu[N] then alpha[N]
   double* ws_d = nullptr;          // per-item workspace blocks
   int n_layers = 0, n_items = 0, n_tasks = 0;
-  int min_n = 0, max_n = 0, max_N = 0;
+  int min_n = 0, max_n = 0, max_N = 0, max_M = 0;
   int trsm_rows = kTrsmRowsDefault;  // right-hand-side rows per FP64 right-division tile (4, 8, 16)
   int trsm_tiles = 0;         // row tiles of the FP64 right division (largest item)
   size_t trsm_lds = 0;        // its LDS bytes
