@@ -170,10 +170,12 @@ extern "C" vbrdf_status vbrdf_solve_noalloc(int32_t N, int32_t L, int32_t M, int
   ls.n_tasks = N * N;
   ls.min_n = ls.max_n = n;
   ls.max_N = N;
-  ls.trsm_rows = kTrsmRows;  // the tile shape its scratch sizes assume
-  ls.trsm_tiles = (n + kTrsmRows - 1) / kTrsmRows;
-  ls.trsm32_tiles = ls.trsm_tiles;
-  ls.trsm_lds = trsm_lds;
+  // the plans' tile shape (16 rows on the matrix cores: 29 against 70 us at N = 16) where its LDS needs no
+  // larger cap than the default, which holds to n = 480
+  ls.trsm_rows = trsm_lds_for(n, kTrsmRowsDefault) <= 65536 ? kTrsmRowsDefault : kTrsmRows;
+  ls.trsm_tiles = trsm_tiles_for(n, ls.trsm_rows);
+  ls.trsm32_tiles = (n + kTrsmRows - 1) / kTrsmRows;
+  ls.trsm_lds = trsm_lds_for(n, ls.trsm_rows);
   ls.eigen_mode = kEigenPlanOrder;  // one layer: every order has the same size
   ls.n_big = n > kLdsMaxn ? M : 0;   // and the same eigensolver kernel (no order table needed)
   enqueue_solve(ls, tau, omega, coef, nullptr, F_r, nullptr, layer_status, s, nullptr);
