@@ -96,6 +96,77 @@ __device__ inline int hess_line(int tid, int P, int NT) {
   return 32 * (hw / P) + P * (l32 / P) + hw % P;
 }
 
+// use(i, load(i)) for i = i0, i0 + step, ... < len, the loads of kHessAhead entries issued together: a line
+// of H in global memory costs one latency for each batch and not for each entry or four.
+constexpr int kHessAhead = 16;
+template <class Load, class Use>
+__device__ __forceinline__ void hess_batches(int i0, int len, int step, Load load, Use use) {
+  for (int b = i0; b < len; b += kHessAhead * step) {
+    double h[kHessAhead];
+#pragma unroll
+    for (int u = 0; u < kHessAhead; ++u) h[u] = load(min(b + u * step, len - 1));
+#pragma unroll
+    for (int u = 0; u < kHessAhead; ++u)
+      if (b + u * step < len) use(b + u * step, h[u]);
+  }
+}
+
+// H <- H (I - tau v v^T) of one step of the reduction, v = (1, scal sv[1 .. len - 1]) on columns k + 1 .., H in
+// global memory, a row per thread. A thread's dot product runs over its row from left to right; read by
+// the row's thread itself, a wave's load would touch 64 lines, so tiles of 16 columns go through LDS. The
+// update has a lane per column. Called by every thread of the workgroup, which has at least n. A call of 256
+// orders at n = 512, which the reduction of its strongly coupled ones bounds: 528 -> 417 ms.
+__device__ void hess_right(double* __restrict__ H, int n, int k, int len, double tau, double scal, const double* sv,
+                           double* sbuf) {
+  constexpr int kW = 16, kLd = kW + 1, kPer = kMaxn * kW / kEigenThreads, kRows = kEigenThreads / kW;
+  static_assert(kEigenThreads >= kMaxn, "a row per thread");
+  static_assert(kMaxn * (kLd + 2) <= kLdsMaxn * (kLdsMaxn + 1), "tile, y and v fit the LDS buffer");
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double* ys = sbuf + kMaxn * kLd;
+  double* vs = ys + kMaxn;
+  for (int i = tid; i < len; i += kEigenThreads) vs[i] = i == 0 ? 1.0 : sv[i] * scal;
+  double* __restrict__ Hk = H + k + 1;
+  const int tr = tid / kW, tc = tid % kW;
+  double h[kPer];
+  auto load = [&](int c0) {
+    const int c = min(c0 + tc, len - 1);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) h[e] = Hk[(int64_t)min(tr + kRows * e, n - 1) * n + c];
+  };
+  load(0);
+  double y = 0.0;
+  for (int c0 = 0; c0 < len; c0 += kW) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) sbuf[(tr + kRows * e) * kLd + tc] = h[e];
+    __syncthreads();
+    if (c0 + kW < len) load(c0 + kW);
+    const int w = min(kW, len - c0);
+    const double* row = sbuf + tid * kLd;
+    if (w == kW) {
+#pragma unroll
+      for (int j = 0; j < kW; ++j) y = fma(row[j], vs[c0 + j], y);
+    } else {
+      for (int j = 0; j < w; ++j) y = fma(row[j], vs[c0 + j], y);
+    }
+  }
+  ys[tid] = tau * y;
+  __syncthreads();
+  for (int r = wv; r < n; r += kEigenThreads / 64) {
+    const double yr = ys[r];
+    double* __restrict__ row = Hk + (int64_t)r * n;
+    for (int c0 = lane; c0 < len; c0 += 4 * 64) {
+      double x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = row[min(c0 + 64 * q, len - 1)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (c0 + 64 * q < len) row[c0 + 64 * q] = fma(-yr, vs[c0 + 64 * q], x[q]);
+    }
+  }
+  __syncthreads();
+}
+
 // ---- Windowed multi-bulge pass for systems kept in global memory (n > kLdsMaxn)
 //
 // Chasing the bulges through H in global memory costs, per chain step and bulge, a read and write
@@ -794,19 +865,34 @@ __device__ __forceinline__ void eigen_body(const Item& it, double* base, int32_t
         double w = 0.0;
         if (c < n) {
           if (part_l == 0) w = HH(k + 1, c) * dlt;
-  #pragma unroll 4
-          for (int i = (part_l == 0 ? Pl : part_l); i < len; i += Pl) w += sv[i] * HH(k + 1 + i, c);
+          const int i0 = part_l == 0 ? Pl : part_l;
+          if constexpr (kLds) {
+#pragma unroll 4
+            for (int i = i0; i < len; i += Pl) w += sv[i] * HH(k + 1 + i, c);
+          } else {
+            hess_batches(i0, len, Pl, [&](int i) { return HH(k + 1 + i, c); }, [&](int i, double h) { w += sv[i] * h; });
+          }
         }
         for (int o = 1; o < Pl; o <<= 1) w += __shfl_xor(w, o);
         w *= tau * scal;
         if (c < n) {
           if (part_l == 0) HH(k + 1, c) -= w;
-  #pragma unroll 4
-          for (int i = (part_l == 0 ? Pl : part_l); i < len; i += Pl) HH(k + 1 + i, c) -= sv[i] * scal * w;
+          const int i0 = part_l == 0 ? Pl : part_l;
+          if constexpr (kLds) {
+#pragma unroll 4
+            for (int i = i0; i < len; i += Pl) HH(k + 1 + i, c) -= sv[i] * scal * w;
+          } else {
+            hess_batches(i0, len, Pl, [&](int i) { return HH(k + 1 + i, c); },
+                         [&](int i, double h) { HH(k + 1 + i, c) = h - sv[i] * scal * w; });
+          }
         }
       }
       __syncthreads();
       // right: H (I - tau v v^T), rows 0..n-1
+      if constexpr (!kLds) {
+        hess_right(H, n, k, len, tau, scal, sv, sH);
+        continue;
+      }
       const int part_r = tid & (Pr - 1);
       for (int r0 = 0; r0 < n; r0 += NT / Pr) {
         const int r = r0 + line_r;
