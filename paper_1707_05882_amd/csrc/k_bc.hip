@@ -14,6 +14,8 @@
 // quadrature-weighted scattering equals the source of eq. 14. A complex pair (columns j, j+1 =
 // real and imaginary parts) is mixed with the complex D of lambda_j, which is the same
 // real-basis change on numerator and denominator.
+#include <type_traits>
+
 #include "vbrdf_internal.hpp"
 
 namespace vbrdf {
@@ -536,22 +538,24 @@ __device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, dou
 //   W L = Z   (descending): W_J = Z_J - W_{>J} L_{>J,J}         (unit diagonal),
 // the products with v_mfma_f64_16x16x4 (A = -Z or -W from LDS: row = lane % 16, k = lane / 16 +
 // 4 t; B = the factor's columns, read from AT where they are contiguous; two accumulators so that
-// consecutive MFMAs do not wait on each other), the 16 x 16 diagonal blocks by substitution in the
-// accumulator layout (row lane / 16 + 4 v, column lane % 16), column c handed to the other lanes
-// by an exchange.
+// consecutive MFMAs do not wait on each other), the 16 x 16 diagonal blocks by substitution with a row
+// per lane, the block's factor read from LDS by all lanes alike (in the accumulator layout, with a column
+// handed to the other lanes by an exchange at each of its 16 steps, the substitution took most of the
+// time: n = 96 62 -> 50 us, n = 128 80 -> 68 us, 9216 systems of n = 128 2.64 -> 1.92 ms).
 constexpr int kTrsmLdz = 17;
 
 // acc -= Zt[:, kb:ke] F[kb:ke, col] for the 16 rows of the tile (ke - kb a multiple of 4; fc a valid
 // column of the factor also for padding lanes, whose results are discarded): chunks of 8 k-steps
 // whose factor loads are issued one chunk ahead. Loads are unconditional (indices clamped) and the
 // k-steps past ke get a zero A operand, so the code has no branches between a load and its use and
-// the next chunk's loads stay in flight over the current chunk's MFMAs.
+// the next chunk's loads stay in flight over the current chunk's MFMAs. bc: the first
+// chunk, loaded by the caller.
+constexpr int kTrsmChunk = 8;
 __device__ __forceinline__ void trsm_block_product(const double* Zt, const double* __restrict__ fc, int n, int kb,
-                                                   int ke, int lr, int kq, double4_t& acc0, double4_t& acc1) {
-  constexpr int kC = 8;
-  double bc[kC], bn[kC];
-#pragma unroll
-  for (int u = 0; u < kC; ++u) bc[u] = fc[min(kb + 4 * u + kq, n - 1)];
+                                                   int ke, int lr, int kq, double (&bc)[kTrsmChunk],
+                                                   double4_t& acc0, double4_t& acc1) {
+  constexpr int kC = kTrsmChunk;
+  double bn[kC];
   for (int k = kb; k < ke; k += 4 * kC) {
 #pragma unroll
     for (int u = 0; u < kC; ++u) bn[u] = fc[min(k + 4 * kC + 4 * u + kq, n - 1)];
@@ -582,20 +586,13 @@ __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0
   const int* __restrict__ pm = lu_perm(ex, n, which);
   HIP_DYNAMIC_SHARED(double, Zt)
   const int nr = min(16, n - r0);
-  // the tile's rows, 8 loads in flight per lane
-  for (int t0 = 0; t0 < 16 * n; t0 += 8 * 64) {
-    double v[8];
+  // the tile's rows, a lane per column, 16 loads in flight
+  for (int c = lane; c < n; c += 64) {
+    double v[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = min(t0 + 64 * u + lane, 16 * n - 1), rr = t / n;
-      v[u] = U[(int64_t)min(r0 + rr, n - 1) * n + t % n];
-      if (rr >= nr) v[u] = 0.0;
-    }
+    for (int r = 0; r < 16; ++r) v[r] = U[(int64_t)min(r0 + r, n - 1) * n + c];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + 64 * u + lane;
-      if (t < 16 * n) Zt[(t % n) * kTrsmLdz + t / n] = v[u];
-    }
+    for (int r = 0; r < 16; ++r) Zt[c * kTrsmLdz + r] = r < nr ? v[r] : 0.0;
   }
   auto sync = [] {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -603,62 +600,76 @@ __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0
   };
   sync();
   const int nblk = (n + 15) >> 4;
-  // Z Uu = B
-  for (int jb = 0; jb < nblk; ++jb) {
-    const int j0 = jb * 16, col = j0 + lr, nv = min(16, n - j0);
-    const bool cl = col < n;
-    const double* __restrict__ fc = AT + (int64_t)(cl ? col : 0) * n;  // column col of the factor
-    // the diagonal block's factor entries and this column's 1 / Uu_jj, loaded ahead of the product
-    double fd[16];
+  double* sD = Zt + n * kTrsmLdz;  // diagonal block of the factor, F(j0 + c, j0 + j) at sD[16 c + j]
+  double* sI = sD + 256;           // and 1 / Uu_jj of its columns
+  // what a block needs of the factor first: its diagonal block, pivots and the first chunk of its product
+  double fd[4], dinv, bc[kTrsmChunk];
+  auto fetch = [&](int j0, int kb) {
+    const int colc = min(j0 + lr, n - 1);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) fd[c] = fc[min(j0 + c, n - 1)];
+    for (int q = 0; q < 4; ++q) fd[q] = AT[(int64_t)min(j0 + 4 * q + kq, n - 1) * n + colc];
+    dinv = id[colc];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) fd[c] = c < lr ? fd[c] : 0.0;  // Uu(j0 + c, col)
-    const double dinv = id[min(col, n - 1)];
+    for (int u = 0; u < kTrsmChunk; ++u) bc[u] = AT[(int64_t)colc * n + min(kb + 4 * u + kq, n - 1)];
+  };
+  // One block of 16 columns from j0: product over the blocks already solved, then the substitution with the
+  // rows in the lanes (row lane % 16, by all four groups of lanes alike) and their 16 entries in registers,
+  // over which the loads of the next block, from jn with the product from kn, are in flight.
+  auto block = [&](int j0, auto lower, int jn, int kn) {
+    constexpr bool kLower = decltype(lower)::value;
+    const int col = j0 + lr, nv = min(16, n - j0), colc = min(col, n - 1);
     double4_t acc0, acc1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc0[v] = Zt[min(col, n - 1) * kTrsmLdz + kq + 4 * v];
-    trsm_block_product(Zt, fc, n, 0, j0, lr, kq, acc0, acc1);
+    for (int v = 0; v < 4; ++v) acc0[v] = Zt[colc * kTrsmLdz + kq + 4 * v];
+    const double* __restrict__ fc = AT + (int64_t)colc * n;  // column col of the factor
+    if (kLower)
+      trsm_block_product(Zt, fc, n, j0 + 16, n, lr, kq, bc, acc0, acc1);
+    else
+      trsm_block_product(Zt, fc, n, 0, j0, lr, kq, bc, acc0, acc1);
     acc0 += acc1;
+    if (col < n)
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      if (c < nv) {  // uniform
-        if (lr == c) acc0 *= dinv;
+      for (int v = 0; v < 4; ++v) Zt[col * kTrsmLdz + kq + 4 * v] = acc0[v];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc0[v] -= __shfl(acc0[v], (kq << 4) | c) * fd[c];
+    for (int q = 0; q < 4; ++q) sD[16 * lr + 4 * q + kq] = fd[q];
+    sI[lr] = dinv;
+    fetch(jn, kn);
+    sync();
+    // late: 0, but known only with the steps before, so that the factor's reads, which the compiler would issue
+    // all at once (256 registers, half the waves), come four steps at a time
+    int late = 0;
+    double x[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) x[c] = Zt[min(j0 + c, n - 1) * kTrsmLdz + lr];
+    if (kLower) {
+#pragma unroll
+      for (int c = 15; c > 0; --c)
+        if (c < nv) {  // uniform
+          if (c % 4 == 3) asm volatile("" : "+v"(late), "+v"(x[c]));
+#pragma unroll
+          for (int j = 0; j < c; ++j) x[j] = fma(-x[c], sD[late + 16 * c + j], x[j]);
+        }
+    } else {
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        x[c] *= sI[c];
+        if (c % 4 == 3) asm volatile("" : "+v"(late), "+v"(x[c]));
+#pragma unroll
+        for (int j = c + 1; j < 16; ++j) x[j] = fma(-x[c], sD[late + 16 * c + j], x[j]);
       }
     }
-    if (cl)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Zt[col * kTrsmLdz + kq + 4 * v] = acc0[v];
     sync();
-  }
-  // W L = Z
-  for (int jb = nblk - 1; jb >= 0; --jb) {
-    const int j0 = jb * 16, col = j0 + lr, nv = min(16, n - j0);
-    const bool cl = col < n;
-    const double* __restrict__ fc = AT + (int64_t)(cl ? col : 0) * n;
-    double fd[16];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) fd[c] = fc[min(j0 + c, n - 1)];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) fd[c] = (c > lr && c < nv) ? fd[c] : 0.0;  // L(j0 + c, col)
-    double4_t acc0, acc1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc0[v] = Zt[min(col, n - 1) * kTrsmLdz + kq + 4 * v];
-    trsm_block_product(Zt, fc, n, j0 + 16, n, lr, kq, acc0, acc1);
-    acc0 += acc1;
-#pragma unroll
-    for (int c = 15; c > 0; --c) {
-      if (c < nv)  // uniform
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc0[v] -= __shfl(acc0[v], (kq << 4) | c) * fd[c];
-    }
-    if (cl)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Zt[col * kTrsmLdz + kq + 4 * v] = acc0[v];
+    for (int c = 0; c < 16; ++c)
+      if (c < nv) Zt[(j0 + c) * kTrsmLdz + lr] = x[c];
     sync();
-  }
+  };
+  const int jl = 16 * (nblk - 1);
+  fetch(0, 0);
+  for (int j0 = 0; j0 <= jl; j0 += 16)  // Z Uu = B
+    block(j0, std::false_type{}, min(j0 + 16, jl), j0 < jl ? 0 : jl + 16);
+  for (int j0 = jl; j0 >= 0; j0 -= 16)  // W L = Z
+    block(j0, std::true_type{}, max(j0 - 16, 0), max(j0, 16));
   // Y[:, perm[c]] = W[:, c]
   for (int c0 = 0; c0 < n; c0 += 64) {
     const int c = c0 + lane;

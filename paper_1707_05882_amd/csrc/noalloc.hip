@@ -171,7 +171,7 @@ extern "C" vbrdf_status vbrdf_solve_noalloc(int32_t N, int32_t L, int32_t M, int
   ls.min_n = ls.max_n = n;
   ls.max_N = N;
   // the plans' tile shape (16 rows on the matrix cores: 29 against 70 us at N = 16) where its LDS needs no
-  // larger cap than the default, which holds to n = 480
+  // larger cap than the default, which holds to n = 464
   ls.trsm_rows = trsm_lds_for(n, kTrsmRowsDefault) <= 65536 ? kTrsmRowsDefault : kTrsmRows;
   ls.trsm_tiles = trsm_tiles_for(n, ls.trsm_rows);
   ls.trsm32_tiles = (n + kTrsmRows - 1) / kTrsmRows;
