@@ -1030,17 +1030,27 @@ __global__ __launch_bounds__(256) void k_resid(const Item* items, double* ws, co
   double4_r acc[2][2];
   for (int a = 0; a < 2; ++a)
     for (int b = 0; b < 2; ++b) acc[a][b] = (double4_r){0.0, 0.0, 0.0, 0.0};
+  // the next step's tiles load over the current one's products, as in k_gemm (n = 96: 66 -> 44 us)
+  double ra[4], rb[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = tid + 256 * q;
+      ra[q] = Y[(int64_t)min(r0 + t / 16, n - 1) * n + min(k0 + t % 16, n - 1)];
+      rb[q] = A[(int64_t)min(k0 + t / 64, n - 1) * n + min(c0 + t % 64, n - 1)];
+    }
+  };
+  load(0);
   for (int k0 = 0; k0 < n; k0 += 16) {
     __syncthreads();
-    for (int t = tid; t < 64 * 16; t += 256) {
-      const int k = t % 16, r = t / 16;
-      sA[r][k] = (r0 + r < n && k0 + k < n) ? Y[(int64_t)(r0 + r) * n + k0 + k] : 0.0;
-    }
-    for (int t = tid; t < 16 * 64; t += 256) {
-      const int c = t % 64, k = t / 64;
-      sB[k][c] = (k0 + k < n && c0 + c < n) ? A[(int64_t)(k0 + k) * n + c0 + c] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = tid + 256 * q;
+      sA[t / 16][t % 16] = k0 + t % 16 < n ? ra[q] : 0.0;
+      sB[t / 64][t % 64] = k0 + t / 64 < n ? rb[q] : 0.0;
     }
     __syncthreads();
+    if (k0 + 16 < n) load(k0 + 16);
 #pragma unroll
     for (int kk = 0; kk < 16; kk += 4) {
       double a[2], b[2];

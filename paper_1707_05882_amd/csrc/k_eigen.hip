@@ -2201,9 +2201,13 @@ __global__ __launch_bounds__(64) void k_hqapply_mfma(const Item* items, int n_it
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  for (int t = lane; t < n * 16; t += 64) {
-    const int r = t >> 4, c = t & 15;
-    sb[r * kHqLd + c] = c < nc ? Up[(int64_t)r * n + c0 + c] : 0.0;
+  for (int r0 = 0; r0 < n; r0 += 32) {  // 8 loads in flight, four rows each (n = 96: 86 -> 78 us)
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = Up[(int64_t)min(r0 + 4 * u + kq, n - 1) * n + c0 + min(lr, nc - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (r0 + 4 * u < n) sb[(r0 + 4 * u + kq) * kHqLd + lr] = lr < nc ? v[u] : 0.0;  // n is a multiple of 4
   }
   sync();
   // V[row][j] (zero off the reflector's support or for tau_j = 0)
