@@ -58,7 +58,7 @@ def stage_work(stage, layers):
     return "alu", fl, "TFLOP/s"
 
 
-KERNEL_SOURCE = {"k_eigen": "k_eigen.hip", "k_eigen_lds": "k_eigen_lds.hip", "k_weak_eigen": "k_weak.hip", "k_eigen_big": "k_eigen.hip", "k_hqapply": "k_eigen.hip", "k_hqapply_mfma": "k_eigen.hip", "k_lu": "k_bc.hip", "k_lu_reg": "k_lu.hip", "k_trsm": "k_bc.hip", "k_vfix": "k_bc.hip",
+KERNEL_SOURCE = {"k_eigen": "k_eigen.hip", "k_eigen_lds": "k_eigen_lds.hip", "k_weak_eigen": "k_weak.hip", "k_eigen_big": "k_eigen.hip", "k_hqapply": "k_eigen.hip", "k_hqapply_mfma": "k_eigen.hip", "k_lu": "k_bc.hip", "k_lu_reg": "k_lu.hip", "k_lu_mid": "k_lu.hip", "k_trsm": "k_bc.hip", "k_vfix": "k_bc.hip",
                  "k_bcbuild": "k_bc.hip", "k_colscal": "k_bc.hip", "k_response": "k_bc.hip", "k_gemm": "k_gemm.hip",
                  "k_assemble": "k_assemble.hip", "k_legendre": "k_assemble.hip", "k_validate": "k_assemble.hip",
                  "k_synth": "k_synth.hip", "k_synth_mfma": "k_synth.hip", "k_refine": "k_refine.hip"}
@@ -67,13 +67,13 @@ KERNEL_SOURCE = {"k_eigen": "k_eigen.hip", "k_eigen_lds": "k_eigen_lds.hip", "k_
 def stage_kernels(stage):
     """Kernels whose launches make up a stage (the eigen stage launches one kernel for the weakly coupled
     orders of large batches, one for the systems held in LDS and one for the larger ones, the lu stage
-    one for the systems held in registers and one for the larger ones)."""
+    one for the systems held in registers and two for the larger ones)."""
     if stage.startswith("gemm"):
         return ["k_gemm"]
     if stage == "eigen":
         return ["k_weak_eigen", "k_eigen_lds", "k_eigen_big"]
     if stage == "lu":
-        return ["k_lu_reg", "k_lu"]
+        return ["k_lu_reg", "k_lu_mid", "k_lu"]
     return [f"k_{stage}"]
 
 

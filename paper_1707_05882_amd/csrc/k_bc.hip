@@ -379,13 +379,13 @@ __device__ inline int* lu_perm(double* ex, int n, int which) {
 }
 
 // LU factorisation with partial pivoting of buffer b.src[side] (side = blockIdx.y), P^T A = L Uu, of the
-// systems of more than kLuRegMaxn rows: in place and blocked. The factor is written
+// systems of more than kLuMidMaxn rows: in place and blocked. The factor is written
 // transposed into b.dst[side], AT[j n + c] = A(c, j), so that column j of Uu (c < j) and of L
 // (c > j) are contiguous for the right division; pivots and 1 / Uu_kk go to the extras block.
 // The source buffer is overwritten.
 __global__ __launch_bounds__(kLuThreadsBig) void k_lu(const Item* items, double* ws, int32_t* status, LuBufs b) {
   const Item it = items[blockIdx.x];
-  if (status[it.layer] != 0 || it.n <= kLuRegMaxn || weak_done(b.skip_weak, ws, it)) return;
+  if (status[it.layer] != 0 || it.n <= kLuMidMaxn || weak_done(b.skip_weak, ws, it)) return;
   const int n = it.n, tid = threadIdx.x, NT = blockDim.x;
   const int which = blockIdx.y;
   double* base = ws + it.ws;
@@ -422,7 +422,8 @@ void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t*
   else if (min_n <= 128)
     k_lu_reg<8><<<grid, 64 * 9, 0, s>>>(items, ws, status, b, 0);
   if (max_n > 128 && min_n <= kLuRegMaxn) k_lu_reg<12><<<grid, 64 * 13, 0, s>>>(items, ws, status, b, 128);
-  if (max_n > kLuRegMaxn) k_lu<<<grid, kLuThreadsBig, 0, s>>>(items, ws, status, b);
+  if (max_n > kLuRegMaxn && min_n <= kLuMidMaxn) k_lu_mid<<<grid, kLuThreadsBig, 0, s>>>(items, ws, status, b);
+  if (max_n > kLuMidMaxn) k_lu<<<grid, kLuThreadsBig, 0, s>>>(items, ws, status, b);
 }
 
 // Right division Y = B A^-1 with the factors of k_lu (S' and T' with B = U in the boundary solve,

@@ -450,6 +450,133 @@ __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, dou
         if (lane + 64 * i < n) AT[(int64_t)(j0 + j) * n + lane + 64 * i] = x[j][i];
   }
 }
+// The systems of kLuRegMaxn < n <= kLuMidMaxn rows, in place: panels of 16 columns by wave 0 as above (four rows
+// in each lane), the matrix in global memory. Then a wave per block of 16 columns to the right: U12 =
+// L11^-1 A12 by forward substitution, in the B-operand layout of v_mfma_f64_16x16x4 (x[t] = row 4 t +
+// lane / 16, column lane % 16), and A22 -= L21 U12 in 16 x 16 tiles, the next tile loading meanwhile.
+// The order of operations on an element is k_lu's, whose panels (a barrier for each of four phases of a column,
+// 5 k cycles) took most of its time: 1536 systems of n = 256 7.15 -> 3.47 ms. Above 256 rows a lane's share no longer fits its registers.
+__global__ __launch_bounds__(kLuThreadsBig) void k_lu_mid(const Item* items, double* ws, int32_t* status, LuBufs b) {
+  const Item it = items[blockIdx.x];
+  if (status[it.layer] != 0 || it.n <= kLuRegMaxn || it.n > kLuMidMaxn || weak_done(b.skip_weak, ws, it)) return;
+  constexpr int kPer = kLuMidMaxn / 64, kLd = kLuMidMaxn + 1, NT = kLuThreadsBig, nw = NT / 64;
+  __shared__ double S[16 * kLd], P[16 * kLd], sL[16 * 17];
+  __shared__ int perm[kLuMidMaxn], bad;
+  const int n = it.n, which = blockIdx.y, tid = threadIdx.x, lane = tid & 63, lr = lane & 15, kq = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double* base = ws + it.ws;
+  double* ex = base + extras_off(n);
+  if (b.only_flagged && !boundary_flags(ex, n)->fallback[which]) return;
+  double* __restrict__ A = buf_ptr(ws, it, b.src[which]);
+  double* __restrict__ AT = buf_ptr(ws, it, b.dst[which]);
+  double* id = ex + (4 + which) * (int64_t)n;
+  int* pm = reinterpret_cast<int*>(ex + 2 * (int64_t)n) + which * n;
+  for (int i = tid; i < n; i += NT) perm[i] = i;
+  if (tid == 0) bad = 0;
+  __syncthreads();
+  for (int k0 = 0; k0 < n; k0 += 16) {
+    const int m = n - k0, w = min(16, m);
+    if (wv == 0) {
+      double a[kPer][16];
+      int pos[kPer], row[kPer];
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int r = lane + 64 * i;
+        row[i] = perm[k0 + min(r, m - 1)];
+        pos[i] = r < m ? k0 + r : -1;
+        const double* __restrict__ ar = A + (int64_t)row[i] * n + k0;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a[i][c] = ar[min(c, w - 1)];
+      }
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+#pragma unroll
+        for (int c = 4; c < 16; ++c) a[i][c] = c < w ? a[i][c] : 0.0;  // w is a multiple of 4
+      lu_panel<kPer>(a, pos, k0, S, kLd);
+      int pivots = 0;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int r = lane + 64 * i, t = pos[i] - k0;
+        bool good = false;
+        if (r < m) {
+          perm[pos[i]] = row[i];
+#pragma unroll
+          for (int c = 0; c < 16; ++c) P[c * kLd + t] = S[c * kLd + r];
+          if (t < w) {
+            const double d = S[t * kLd + r];
+            good = d != 0.0 && isfinite(d);
+            id[pos[i]] = 1.0 / d;
+          }
+        }
+        pivots += __popcll(__ballot(good));
+      }
+      if (pivots != w && lane == 0) {
+        bad = 1;
+        status[it.layer] = -5;
+      }
+    }
+    __syncthreads();
+    if (bad) return;
+    for (int t = tid; t < m * 16; t += NT)
+      if (t % 16 < w) A[(int64_t)perm[k0 + t / 16] * n + k0 + t % 16] = P[(t % 16) * kLd + t / 16];
+    const int r0 = k0 + 16;
+    if (r0 >= n) break;
+    if (tid < 256) {  // strictly lower part of L11, zeros elsewhere
+      const int s = tid / 16, r = tid % 16;
+      sL[s * 17 + r] = r > s ? P[s * kLd + r] : 0.0;
+    }
+    __syncthreads();
+    const int nrest = n - r0;
+    for (int cb = wv; cb * 16 < nrest; cb += nw) {
+      const int col = r0 + cb * 16 + lr, colc = min(col, n - 1);
+      const bool live = col < n;
+      double x[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) x[t] = A[(int64_t)perm[k0 + 4 * t + kq] * n + colc];
+      double nx[4];  // the next tile of A22
+      auto load = [&](int rb) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) nx[v] = A[(int64_t)perm[min(r0 + rb * 16 + kq + 4 * v, n - 1)] * n + colc];
+      };
+      load(0);
+#pragma unroll
+      for (int s = 0; s < 15; ++s) {
+        const double xs = __shfl(x[s >> 2], ((s & 3) << 4) | lr);
+#pragma unroll
+        for (int t = s >> 2; t < 4; ++t) x[t] -= sL[s * 17 + 4 * t + kq] * xs;
+      }
+      if (live)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) A[(int64_t)perm[k0 + 4 * t + kq] * n + col] = x[t];
+      for (int rb = 0; rb * 16 < nrest; ++rb) {
+        double4_t acc = {nx[0], nx[1], nx[2], nx[3]};
+        load(rb + 1);
+        const int pi = min(16 + rb * 16 + lr, m - 1);  // rows past the end are not stored
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-P[(4 * t + kq) * kLd + pi], x[t], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int pos = r0 + rb * 16 + kq + 4 * v;
+          if (pos < n && live) A[(int64_t)perm[pos] * n + col] = acc[v];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // the factor transposed and in its final order, 16 columns at a time through LDS
+  __syncthreads();
+  for (int j0 = 0; j0 < n; j0 += 16) {
+    const int w = min(16, n - j0);
+    for (int t = tid; t < n * 16; t += NT) S[(t % 16) * kLd + t / 16] = A[(int64_t)perm[t / 16] * n + min(j0 + t % 16, n - 1)];
+    __syncthreads();
+    for (int j = wv; j < w; j += nw)
+      for (int c = lane; c < n; c += 64) AT[(int64_t)(j0 + j) * n + c] = S[j * kLd + c];
+    __syncthreads();
+  }
+  for (int i = tid; i < n; i += NT) pm[i] = perm[i];
+}
+
 template __global__ void k_lu_reg<4>(const Item*, double*, int32_t*, LuBufs, int);
 template __global__ void k_lu_reg<8>(const Item*, double*, int32_t*, LuBufs, int);
 template __global__ void k_lu_reg<12>(const Item*, double*, int32_t*, LuBufs, int);

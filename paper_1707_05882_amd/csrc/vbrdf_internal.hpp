@@ -208,12 +208,13 @@ __global__ void k_trsm32(const Item* items, int n_items, int tiles, double* ws, 
 __global__ void k_resid(const Item* items, double* ws, const int32_t* status);
 __global__ void k_bcheck(const Item* items, double* ws, int32_t* status, int no_fallback);
 // LU with partial pivoting. k_lu_reg<kT> (k_lu.hip): systems of n_above < n <= 16 kT rows, kT + 1 waves;
-// k_lu: the systems of more than kLuRegMaxn rows, blocked, a thread per row. launch_lu issues those of
+// k_lu_mid: up to kLuMidMaxn rows; k_lu: the larger ones, blocked, a thread per row. launch_lu issues those of
 // the size classes between the smallest and the largest system (min_n = 0: from the smallest).
-constexpr int kLuRegMaxn = 192, kLuThreadsBig = 512;
+constexpr int kLuRegMaxn = 192, kLuMidMaxn = 256, kLuThreadsBig = 512;
 static_assert(kLuThreadsBig >= kMaxn && kLuThreadsBig % 64 == 0, "a thread per row in the blocked LU");
 template <int kT>
 __global__ void k_lu_reg(const Item* items, double* ws, int32_t* status, LuBufs b, int n_above);
+__global__ void k_lu_mid(const Item* items, double* ws, int32_t* status, LuBufs b);
 __global__ void k_lu(const Item* items, double* ws, int32_t* status, LuBufs b);
 void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t* status, int min_n, int max_n,
                LuBufs b);

@@ -1,4 +1,4 @@
-"""The factorisation with the matrix in registers at the edges of its tiles and forms (64, 128 and 192 rows,
+"""The factorisation with the matrix in registers at the edges of its tiles and forms (64, 128, 192 and 256 rows,
 the blocked form above): the form for up to 64 rows and the one for up to 128 do the same operations in the
 same order, so a layer has the same bits by either; beyond 128 rows the per-order responses of a strongly
 coupled layer are within 1e-9 of the layer's largest (the gate of the general solver)."""
@@ -36,7 +36,7 @@ def test_same_bits_beside_a_larger_layer(N):
     assert torch.equal(alone, beside)
 
 
-@pytest.mark.parametrize("N", [17, 31, 32, 33, 36, 37, 47, 48, 49])
+@pytest.mark.parametrize("N", [17, 31, 32, 33, 36, 37, 47, 48, 49, 51, 63, 64, 65])
 def test_sizes_against_oracle(N):
     c, tau, om = layer(N)
     s = BRDFSolver([N], [40], [2], [3])
