@@ -414,7 +414,7 @@ vbrdf_status vbrdf_plan_create(const vbrdf_plan_desc* d, vbrdf_plan** out) {
     p->max_n = std::max(p->max_n, n);
     p->max_M = std::max(p->max_M, ly.M);
     p->min_n = p->min_n ? std::min(p->min_n, n) : n;
-    p->trsm32_tiles = std::max(p->trsm32_tiles, (n + kTrsmRows - 1) / kTrsmRows);
+    p->trsm32_tiles = std::max(p->trsm32_tiles, (n + kTrsm32Rows - 1) / kTrsm32Rows);
     p->max_N = std::max(p->max_N, ly.N);
     coef_off += 6 * (int64_t)ly.L;
     out_off += (int64_t)ly.N * ly.N * ly.n_dphi * 16;
@@ -707,7 +707,7 @@ void enqueue_solve(const LaunchSet& ls, const double* tau, const double* omega, 
   if (p->precision == VBRDF_PRECISION_FP32_REFINED) {
     // FP32 factorisations and right divisions, refined against FP64 residuals; sides that do not
     // converge are redone in FP64 (or reported NONCONVERGED when the fallback is disabled)
-    const size_t lds32 = sizeof(float) * (size_t)mn * (kTrsmRows + 1 + 2);
+    const size_t lds32 = trsm_lds_for(mn, kTrsm32Rows) / 2;  // floats
     const dim3 rg(gt, gt, 2 * ni);
     k_lu32<<<dim3(ni, 2), 1024, 0, s>>>(p->items_d, p->ws_d, layer_status);
     mark();

@@ -436,29 +436,25 @@ void launch_lu(dim3 grid, hipStream_t s, const Item* items, double* ws, int32_t*
 //   W L = Z  :  W_j = Z_j - sum_{c>j} W_c L_cj                 (j descending, unit L)
 // and Y[:, perm[j]] = W[:, j]. The factor column used at step j is the same for all rows: the
 // wave stages it in LDS while the loads of the next column are in flight.
-// TF: type of the factor and of the arithmetic (double, or float in the refined path); TB: type
-// of the right-hand side rows (the FP64 U, or an FP32 residual); kAdd: accumulate into Y instead of
-// overwriting it. The right-hand side of side `which` is read at rhs_off doubles from the item base.
 // R: right-hand-side rows per tile (64 / R lanes per row).
-template <int R, int ldb, typename TF, typename TB, bool kAdd>
-__device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, double* ws, const TF* __restrict__ AT,
-                                          const TB* __restrict__ U, double* __restrict__ Y) {
+template <int R, int ldb>
+__device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, double* ws, const double* __restrict__ AT,
+                                          const double* __restrict__ U, double* __restrict__ Y) {
   const int n = it.n, lane = threadIdx.x;
   double* base = ws + it.ws;
   double* ex = base + extras_off(n);
   const double* __restrict__ id = lu_invd(ex, n, which);
   const int* __restrict__ pm = lu_perm(ex, n, which);
   // LDS: Bt [n][ldb], then two factor-column buffers [2][n]
-  HIP_DYNAMIC_SHARED(double, smem_raw)
-  TF* smem = reinterpret_cast<TF*>(smem_raw);
-  TF* Bt = smem;
-  TF* cb = smem + (int64_t)n * ldb;
+  HIP_DYNAMIC_SHARED(double, smem)
+  double* Bt = smem;
+  double* cb = smem + (int64_t)n * ldb;
   const int nr = min(R, n - r0);
   for (int t = lane; t < nr * n; t += 64) {
     const int rr = t / n, c = t % n;
-    Bt[c * ldb + rr] = (TF)U[(int64_t)(r0 + rr) * n + c];
+    Bt[c * ldb + rr] = U[(int64_t)(r0 + rr) * n + c];
   }
-  TF pre[kMaxn / 64];
+  double pre[kMaxn / 64];
   auto fetch = [&](int j) {
 #pragma unroll
     for (int q = 0; q < kMaxn / 64; ++q) {
@@ -466,7 +462,7 @@ __device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, dou
       if (c < n) pre[q] = AT[(int64_t)j * n + c];
     }
   };
-  auto stash = [&](TF* dst) {
+  auto stash = [&](double* dst) {
 #pragma unroll
     for (int q = 0; q < kMaxn / 64; ++q) {
       const int c = lane + 64 * q;
@@ -479,25 +475,25 @@ __device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, dou
   };
   constexpr int kLpr = 64 / R;  // lanes per right-hand-side row
   const int row = lane / kLpr, part = lane % kLpr;
-  TF* b = Bt + row;
+  double* b = Bt + row;
   const bool own = row < nr;
   // Z Uu = U, j ascending
   fetch(0);
   stash(cb);
   sync();
   for (int j = 0; j < n; ++j) {
-    const TF* col = cb + (j & 1) * n;
+    const double* col = cb + (j & 1) * n;
     if (j + 1 < n) fetch(j + 1);
-    TF a0 = 0, a1 = 0;
+    double a0 = 0, a1 = 0;
     int c = part;
     for (; c + kLpr < j; c += 2 * kLpr) {
       a0 -= b[c * ldb] * col[c];
       a1 -= b[(c + kLpr) * ldb] * col[c + kLpr];
     }
     if (c < j) a0 -= b[c * ldb] * col[c];
-    TF acc = a0 + a1;
+    double acc = a0 + a1;
     for (int o = 1; o < kLpr; o <<= 1) acc += __shfl_xor(acc, o);
-    if (own && part == 0) b[j * ldb] = (b[j * ldb] + acc) * (TF)id[j];
+    if (own && part == 0) b[j * ldb] = (b[j * ldb] + acc) * id[j];
     sync();  // the new entry and every read of the buffer the next stash overwrites are done
     if (j + 1 < n) stash(cb + ((j + 1) & 1) * n);
     sync();
@@ -507,16 +503,16 @@ __device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, dou
   stash(cb + ((n - 1) & 1) * n);
   sync();
   for (int j = n - 1; j >= 0; --j) {
-    const TF* col = cb + (j & 1) * n;
+    const double* col = cb + (j & 1) * n;
     if (j > 0) fetch(j - 1);
-    TF a0 = 0, a1 = 0;
+    double a0 = 0, a1 = 0;
     int c = j + 1 + part;
     for (; c + kLpr < n; c += 2 * kLpr) {
       a0 -= b[c * ldb] * col[c];
       a1 -= b[(c + kLpr) * ldb] * col[c + kLpr];
     }
     if (c < n) a0 -= b[c * ldb] * col[c];
-    TF acc = a0 + a1;
+    double acc = a0 + a1;
     for (int o = 1; o < kLpr; o <<= 1) acc += __shfl_xor(acc, o);
     if (own && part == 0) b[j * ldb] += acc;
     sync();
@@ -525,10 +521,7 @@ __device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, dou
   }
   for (int t = lane; t < nr * n; t += 64) {
     const int rr = t / n, c = t % n;
-    if (kAdd)
-      Y[(int64_t)(r0 + rr) * n + pm[c]] += (double)Bt[c * ldb + rr];
-    else
-      Y[(int64_t)(r0 + rr) * n + pm[c]] = (double)Bt[c * ldb + rr];
+    Y[(int64_t)(r0 + rr) * n + pm[c]] = Bt[c * ldb + rr];
   }
 }
 
@@ -543,7 +536,28 @@ __device__ __forceinline__ void trsm_tile(const Item& it, int which, int r0, dou
 // per lane, the block's factor read from LDS by all lanes alike (in the accumulator layout, with a column
 // handed to the other lanes by an exchange at each of its 16 steps, the substitution took most of the
 // time: n = 96 62 -> 50 us, n = 128 80 -> 68 us, 9216 systems of n = 128 2.64 -> 1.92 ms).
+// T: double, or float in the refined path (v_mfma_f32_16x16x4, whose accumulator holds rows 4 (lane / 16) + v;
+// 193 us a launch at n = 96 with a dot product per column, 76 now).
 constexpr int kTrsmLdz = 17;
+
+template <typename T>
+struct TrsmMfma;
+template <>
+struct TrsmMfma<double> {
+  typedef double4_t Acc;
+  static __device__ __forceinline__ Acc madd(double a, double b, Acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int kq, int v) { return kq + 4 * v; }
+};
+template <>
+struct TrsmMfma<float> {
+  typedef float Acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ Acc madd(float a, float b, Acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int kq, int v) { return 4 * kq + v; }
+};
 
 // acc -= Zt[:, kb:ke] F[kb:ke, col] for the 16 rows of the tile (ke - kb a multiple of 4; fc a valid
 // column of the factor also for padding lanes, whose results are discarded): chunks of 8 k-steps
@@ -552,48 +566,52 @@ constexpr int kTrsmLdz = 17;
 // the next chunk's loads stay in flight over the current chunk's MFMAs. bc: the first
 // chunk, loaded by the caller.
 constexpr int kTrsmChunk = 8;
-__device__ __forceinline__ void trsm_block_product(const double* Zt, const double* __restrict__ fc, int n, int kb,
-                                                   int ke, int lr, int kq, double (&bc)[kTrsmChunk],
-                                                   double4_t& acc0, double4_t& acc1) {
+template <typename T>
+__device__ __forceinline__ void trsm_block_product(const T* Zt, const T* __restrict__ fc, int n, int kb, int ke,
+                                                   int lr, int kq, T (&bc)[kTrsmChunk],
+                                                   typename TrsmMfma<T>::Acc& acc0, typename TrsmMfma<T>::Acc& acc1) {
   constexpr int kC = kTrsmChunk;
-  double bn[kC];
+  T bn[kC];
   for (int k = kb; k < ke; k += 4 * kC) {
 #pragma unroll
     for (int u = 0; u < kC; ++u) bn[u] = fc[min(k + 4 * kC + 4 * u + kq, n - 1)];
-    double a[kC];
+    T a[kC];
 #pragma unroll
     for (int u = 0; u < kC; ++u) {
-      const double z = Zt[min(k + 4 * u + kq, n - 1) * kTrsmLdz + lr];
-      a[u] = (k + 4 * u < ke) ? -z : 0.0;
+      const T z = Zt[min(k + 4 * u + kq, n - 1) * kTrsmLdz + lr];
+      a[u] = (k + 4 * u < ke) ? -z : T(0);
     }
 #pragma unroll
     for (int u = 0; u < kC; u += 2) {
-      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], bc[u], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u + 1], bc[u + 1], acc1, 0, 0, 0);
+      acc0 = TrsmMfma<T>::madd(a[u], bc[u], acc0);
+      acc1 = TrsmMfma<T>::madd(a[u + 1], bc[u + 1], acc1);
     }
 #pragma unroll
     for (int u = 0; u < kC; ++u) bc[u] = bn[u];
   }
 }
 
+template <typename T, typename TB, bool kAdd>
 __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0, double* ws,
-                                               const double* __restrict__ AT, const double* __restrict__ U,
+                                               const T* __restrict__ AT, const TB* __restrict__ U,
                                                double* __restrict__ Y) {
+  typedef typename TrsmMfma<T>::Acc Acc;
   const int n = it.n, lane = threadIdx.x;
   const int lr = lane & 15, kq = lane >> 4;
   double* base = ws + it.ws;
   double* ex = base + extras_off(n);
   const double* __restrict__ id = lu_invd(ex, n, which);
   const int* __restrict__ pm = lu_perm(ex, n, which);
-  HIP_DYNAMIC_SHARED(double, Zt)
+  HIP_DYNAMIC_SHARED(double, smem_raw)
+  T* Zt = reinterpret_cast<T*>(smem_raw);
   const int nr = min(16, n - r0);
   // the tile's rows, a lane per column, 16 loads in flight
   for (int c = lane; c < n; c += 64) {
-    double v[16];
+    TB v[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = U[(int64_t)min(r0 + r, n - 1) * n + c];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) Zt[c * kTrsmLdz + r] = r < nr ? v[r] : 0.0;
+    for (int r = 0; r < 16; ++r) Zt[c * kTrsmLdz + r] = r < nr ? (T)v[r] : T(0);
   }
   auto sync = [] {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -601,15 +619,15 @@ __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0
   };
   sync();
   const int nblk = (n + 15) >> 4;
-  double* sD = Zt + n * kTrsmLdz;  // diagonal block of the factor, F(j0 + c, j0 + j) at sD[16 c + j]
-  double* sI = sD + 256;           // and 1 / Uu_jj of its columns
+  T* sD = Zt + n * kTrsmLdz;  // diagonal block of the factor, F(j0 + c, j0 + j) at sD[16 c + j]
+  T* sI = sD + 256;           // and 1 / Uu_jj of its columns
   // what a block needs of the factor first: its diagonal block, pivots and the first chunk of its product
-  double fd[4], dinv, bc[kTrsmChunk];
+  T fd[4], dinv, bc[kTrsmChunk];
   auto fetch = [&](int j0, int kb) {
     const int colc = min(j0 + lr, n - 1);
 #pragma unroll
     for (int q = 0; q < 4; ++q) fd[q] = AT[(int64_t)min(j0 + 4 * q + kq, n - 1) * n + colc];
-    dinv = id[colc];
+    dinv = (T)id[colc];
 #pragma unroll
     for (int u = 0; u < kTrsmChunk; ++u) bc[u] = AT[(int64_t)colc * n + min(kb + 4 * u + kq, n - 1)];
   };
@@ -619,18 +637,18 @@ __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0
   auto block = [&](int j0, auto lower, int jn, int kn) {
     constexpr bool kLower = decltype(lower)::value;
     const int col = j0 + lr, nv = min(16, n - j0), colc = min(col, n - 1);
-    double4_t acc0, acc1 = {0.0, 0.0, 0.0, 0.0};
+    Acc acc0, acc1 = {0, 0, 0, 0};
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc0[v] = Zt[colc * kTrsmLdz + kq + 4 * v];
-    const double* __restrict__ fc = AT + (int64_t)colc * n;  // column col of the factor
+    for (int v = 0; v < 4; ++v) acc0[v] = Zt[colc * kTrsmLdz + TrsmMfma<T>::row(kq, v)];
+    const T* __restrict__ fc = AT + (int64_t)colc * n;  // column col of the factor
     if (kLower)
-      trsm_block_product(Zt, fc, n, j0 + 16, n, lr, kq, bc, acc0, acc1);
+      trsm_block_product<T>(Zt, fc, n, j0 + 16, n, lr, kq, bc, acc0, acc1);
     else
-      trsm_block_product(Zt, fc, n, 0, j0, lr, kq, bc, acc0, acc1);
+      trsm_block_product<T>(Zt, fc, n, 0, j0, lr, kq, bc, acc0, acc1);
     acc0 += acc1;
     if (col < n)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) Zt[col * kTrsmLdz + kq + 4 * v] = acc0[v];
+      for (int v = 0; v < 4; ++v) Zt[col * kTrsmLdz + TrsmMfma<T>::row(kq, v)] = acc0[v];
 #pragma unroll
     for (int q = 0; q < 4; ++q) sD[16 * lr + 4 * q + kq] = fd[q];
     sI[lr] = dinv;
@@ -639,7 +657,7 @@ __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0
     // late: 0, but known only with the steps before, so that the factor's reads, which the compiler would issue
     // all at once (256 registers, half the waves), come four steps at a time
     int late = 0;
-    double x[16];
+    T x[16];
 #pragma unroll
     for (int c = 0; c < 16; ++c) x[c] = Zt[min(j0 + c, n - 1) * kTrsmLdz + lr];
     if (kLower) {
@@ -676,7 +694,15 @@ __device__ __forceinline__ void trsm_tile_mfma(const Item& it, int which, int r0
     const int c = c0 + lane;
     if (c < n) {
       const int64_t pc = pm[c];
-      for (int rr = 0; rr < nr; ++rr) Y[(int64_t)(r0 + rr) * n + pc] = Zt[c * kTrsmLdz + rr];
+      double y[16];
+      if (kAdd)
+#pragma unroll
+        for (int rr = 0; rr < 16; ++rr) y[rr] = Y[(int64_t)min(r0 + rr, n - 1) * n + pc];
+#pragma unroll
+      for (int rr = 0; rr < 16; ++rr)
+        if (rr < nr)
+          Y[(int64_t)(r0 + rr) * n + pc] =
+              kAdd ? y[rr] + (double)Zt[c * kTrsmLdz + rr] : (double)Zt[c * kTrsmLdz + rr];
     }
   }
 }
@@ -701,13 +727,13 @@ __global__ __launch_bounds__(64) void k_trsm(const Item* items, int n_items, int
   // the tile shape and stride are compile-time constants so that LDS offsets fold into the
   // instructions
   if (kRows == 16)
-    trsm_tile_mfma(it, side, r0, ws, AT, U, Y);
+    trsm_tile_mfma<double, double, false>(it, side, r0, ws, AT, U, Y);
   else if (kRows != 8)
-    trsm_tile<kRows, kRows + 1, double, double, false>(it, side, r0, ws, AT, U, Y);
+    trsm_tile<kRows, kRows + 1>(it, side, r0, ws, AT, U, Y);
   else if (trsm_ldb(n) == kTrsmLdb)
-    trsm_tile<kTrsmRows, kTrsmLdb, double, double, false>(it, side, r0, ws, AT, U, Y);
+    trsm_tile<kTrsmRows, kTrsmLdb>(it, side, r0, ws, AT, U, Y);
   else
-    trsm_tile<kTrsmRows, kTrsmRows + 1, double, double, false>(it, side, r0, ws, AT, U, Y);
+    trsm_tile<kTrsmRows, kTrsmRows + 1>(it, side, r0, ws, AT, U, Y);
 }
 template __global__ void k_trsm<4>(const Item*, int, int, double*, int32_t*, TrsmBufs);
 template __global__ void k_trsm<8>(const Item*, int, int, double*, int32_t*, TrsmBufs);
@@ -990,16 +1016,16 @@ __global__ __launch_bounds__(64) void k_trsm32(const Item* items, int n_items, i
     bf->resmax[side] = 0ull;
     if (side == 0) bf->umax = 0ull;
   }
-  const int r0 = tile * kTrsmRows;
+  const int r0 = tile * kTrsm32Rows;
   if (r0 >= n || bf->fallback[side]) return;
   const float* AT = reinterpret_cast<const float*>(base + (int64_t)(side == 0 ? kBufG : kBufF) * n * n);
   double* Y = base + (int64_t)(side == 0 ? kBufYS : kBufYT) * n * n;
   if (accumulate) {
     const float* R = reinterpret_cast<const float*>(base + (int64_t)kBufE * n * n) + (int64_t)side * n * n;
-    trsm_tile<kTrsmRows, kTrsmRows + 1, float, float, true>(it, side, r0, ws, AT, R, Y);
+    trsm_tile_mfma<float, float, true>(it, side, r0, ws, AT, R, Y);
   } else {
     const double* U = base + (int64_t)kBufU * n * n;
-    trsm_tile<kTrsmRows, kTrsmRows + 1, float, double, false>(it, side, r0, ws, AT, U, Y);
+    trsm_tile_mfma<float, double, false>(it, side, r0, ws, AT, U, Y);
   }
 }
 

@@ -174,7 +174,7 @@ extern "C" vbrdf_status vbrdf_solve_noalloc(int32_t N, int32_t L, int32_t M, int
   // larger cap than the default, which holds to n = 464
   ls.trsm_rows = trsm_lds_for(n, kTrsmRowsDefault) <= 65536 ? kTrsmRowsDefault : kTrsmRows;
   ls.trsm_tiles = trsm_tiles_for(n, ls.trsm_rows);
-  ls.trsm32_tiles = (n + kTrsmRows - 1) / kTrsmRows;
+  ls.trsm32_tiles = (n + kTrsm32Rows - 1) / kTrsm32Rows;
   ls.trsm_lds = trsm_lds_for(n, ls.trsm_rows);
   ls.eigen_mode = kEigenPlanOrder;  // one layer: every order has the same size
   ls.n_big = n > kLdsMaxn ? M : 0;   // and the same eigensolver kernel (no order table needed)

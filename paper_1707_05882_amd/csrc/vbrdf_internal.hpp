@@ -235,9 +235,9 @@ __global__ void k_refine_pairs(const Item* items, double* ws, const int32_t* sta
 __global__ void k_refine_delta(const Item* items, double* ws, const int32_t* status, int weak);
 __global__ void k_refine_commit(const Item* items, double* ws, const int32_t* status, int weak);
 // right-hand-side rows per right-division tile (one wave, 64 / kTrsmRows lanes per row; the tile takes
-// n x (trsm_ldb(n) + 2) doubles of LDS). The FP32 right division uses this shape; the FP64 one starts
-// from kTrsmRowsDefault, the 16-row tile whose products run on the matrix cores.
-constexpr int kTrsmRows = 8;
+// n x (trsm_ldb(n) + 2) doubles of LDS). The FP64 right division starts from
+// kTrsmRowsDefault, the 16-row tile whose products run on the matrix cores; the FP32 one has that shape.
+constexpr int kTrsmRows = 8, kTrsm32Rows = 16;
 constexpr int kTrsmRowsDefault = 16;
 // LDS row stride of the right-division tile, in doubles. A 64-bit LDS access is served 16 lanes
 // at a time over 32 banks: 8 parts x 2 rows at offsets 18 part + row = 2 part + row (mod 16) meet
@@ -307,7 +307,7 @@ struct LaunchSet {
   int trsm_rows = kTrsmRowsDefault;  // right-hand-side rows per FP64 right-division tile (4, 8, 16)
   int trsm_tiles = 0;         // row tiles of the FP64 right division (largest item)
   size_t trsm_lds = 0;        // its LDS bytes
-  int trsm32_tiles = 0;       // row tiles of the FP32 right division (kTrsmRows rows each)
+  int trsm32_tiles = 0;       // row tiles of the FP32 right division (kTrsm32Rows rows each)
   int eigen_mode = 0;         // k_eigen scheduling: kEigenPlanOrder / kEigenLongestFirst / kEigenPersistent
   const int32_t* order_d = nullptr;       // items longest first, those with n > kLdsMaxn in front
   const int32_t* order_plan_d = nullptr;  // items in plan order, the low orders first (null: plan order)
