@@ -112,8 +112,8 @@ vbrdf_status upload(const std::vector<T>& h, T** d) {
 
 // Whether the solve runs the iteration for weakly coupled orders first. It frees compute units, so it
 // pays where the general eigensolver would need more than one round of them (one problem per unit),
-// or where its problems contend for the memory (n > 256: 256 orders at n = 512 took 851 ms, with the
-// 10 strongly coupled ones left to it 443 ms); below that the strongly coupled orders bound the stage
+// or where its problems contend for the memory (n > 256: a call of 256 orders at n = 512 took 868 ms, with
+// the faint ones out of it 532 ms); below that the strongly coupled orders bound the stage
 // either way and the iteration only delays them (64 orders at n = 128: 4.56 against 4.83 ms). Not with
 // a cap on the QR sweeps (a forced failure, which needs every order to go by the QR), and not where
 // the adjoint's state is kept: its gradients amplify the rounding of the eigenvectors of weak orders
