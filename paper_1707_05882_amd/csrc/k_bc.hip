@@ -385,7 +385,7 @@ __device__ inline int* lu_perm(double* ex, int n, int which) {
 // The source buffer is overwritten.
 __global__ __launch_bounds__(kLuThreadsBig) void k_lu(const Item* items, double* ws, int32_t* status, LuBufs b) {
   const Item it = items[blockIdx.x];
-  if (status[it.layer] != 0 || it.n <= kLuMidMaxn || weak_done(b.skip_weak, ws, it)) return;
+  if (it.n <= kLuMidMaxn || layer_failed(status, it.layer) || weak_done(b.skip_weak, ws, it)) return;
   const int n = it.n, tid = threadIdx.x, NT = blockDim.x;
   const int which = blockIdx.y;
   double* base = ws + it.ws;
@@ -904,7 +904,7 @@ __device__ __forceinline__ void vfix_body(const Item& it, double* base, int32_t*
 
 __global__ __launch_bounds__(256) void k_vfix(const Item* items, double* ws, int32_t* status) {
   const Item it = items[blockIdx.x];
-  if (status[it.layer] != 0) return;
+  if (layer_failed(status, it.layer)) return;
   double* base = ws + it.ws;
   __shared__ double smem[kVfixLds];
   __shared__ int perm[2 * kMaxn];

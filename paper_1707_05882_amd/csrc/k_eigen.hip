@@ -2035,7 +2035,7 @@ __device__ __forceinline__ void eigen_body(const Item& it, double* base, int32_t
 __global__ __launch_bounds__(kEigenThreads) void k_eigen(const Item* items, double* ws, int32_t* status,
                                                           int sweep_cap, const int32_t* order, int) {
   const Item it = items[order ? order[blockIdx.x] : blockIdx.x];
-  if (status[it.layer] != 0 || it.n > kLdsMaxn) return;
+  if (it.n > kLdsMaxn || layer_failed(status, it.layer)) return;
   __shared__ double sH[kLdsMaxn * (kLdsMaxn + 1) + 3 * 64];
   __shared__ double srefl[2 * 3 * kMaxn];
   __shared__ double sred[16];
@@ -2052,7 +2052,7 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen(const Item* items, doub
 __global__ __launch_bounds__(kEigenThreads) void k_eigen_big(const Item* items, double* ws, int32_t* status,
                                                               int sweep_cap, const int32_t* order, int weak) {
   const Item it = items[order ? order[blockIdx.x] : blockIdx.x];
-  if (status[it.layer] != 0 || it.n <= kLdsMaxn || weak_done(weak, ws, it)) return;
+  if (it.n <= kLdsMaxn || layer_failed(status, it.layer) || weak_done(weak, ws, it)) return;
   __shared__ double sbuf[kWin * kWinLd + kWin * kWinU];
   __shared__ double srefl[2 * 3 * kMaxn];
   __shared__ double sred[16];
@@ -2082,7 +2082,7 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen_persistent(const Item* 
     const int pos = snext;
     if (pos >= n_items) return;
     const Item it = items[order[pos]];
-    if (status[it.layer] != 0 || it.n > kLdsMaxn) continue;
+    if (it.n > kLdsMaxn || layer_failed(status, it.layer)) continue;
     eigen_body<true>(it, ws + it.ws, status, sH, srefl, sred, sctl, sxyz, zops, sweep_cap);
   }
 }

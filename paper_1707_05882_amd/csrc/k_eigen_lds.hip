@@ -986,7 +986,7 @@ __device__ __forceinline__ void lds_eigen(const Item& it, double* base, int32_t*
 __global__ __launch_bounds__(kEigenThreads) void k_eigen_lds(const Item* items, double* ws, int32_t* status, int sweep_cap,
                                                               const int32_t* order, int weak) {
   const Item it = items[order ? order[blockIdx.x] : blockIdx.x];
-  if (status[it.layer] != 0 || it.n > kLdsMaxn || weak_done(weak, ws, it)) return;
+  if (it.n > kLdsMaxn || layer_failed(status, it.layer) || weak_done(weak, ws, it)) return;
   __shared__ EigenLds s;
   lds_eigen(it, ws + it.ws, status, s, sweep_cap);
 }
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen_lds_persistent(const It
     const int pos = snext;
     if (pos >= n_items) return;
     const Item it = items[order[pos]];
-    if (status[it.layer] != 0 || it.n > kLdsMaxn || weak_done(weak, ws, it)) continue;
+    if (it.n > kLdsMaxn || layer_failed(status, it.layer) || weak_done(weak, ws, it)) continue;
     lds_eigen(it, ws + it.ws, status, s, sweep_cap);
   }
 }

@@ -280,7 +280,7 @@ template <int kT>
 __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, double* ws, int32_t* status, LuBufs b,
                                                           int n_above) {
   const Item it = items[blockIdx.x];
-  if (status[it.layer] != 0 || it.n <= n_above || it.n > 16 * kT || weak_done(b.skip_weak, ws, it)) return;
+  if (it.n <= n_above || it.n > 16 * kT || layer_failed(status, it.layer) || weak_done(b.skip_weak, ws, it)) return;
   constexpr int kPer = (kT + 3) / 4;
   // who solves for U12: the panel wave, or, where its 48 columns a lane leave no registers, those with tiles
   constexpr bool kWide = kPer < 3;
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, dou
 // 5 k cycles) took most of its time: 1536 systems of n = 256 7.15 -> 3.47 ms. Above 256 rows a lane's share no longer fits its registers.
 __global__ __launch_bounds__(kLuThreadsBig) void k_lu_mid(const Item* items, double* ws, int32_t* status, LuBufs b) {
   const Item it = items[blockIdx.x];
-  if (status[it.layer] != 0 || it.n <= kLuRegMaxn || it.n > kLuMidMaxn || weak_done(b.skip_weak, ws, it)) return;
+  if (it.n <= kLuRegMaxn || it.n > kLuMidMaxn || layer_failed(status, it.layer) || weak_done(b.skip_weak, ws, it)) return;
   constexpr int kPer = kLuMidMaxn / 64, kLd = kLuMidMaxn + 1, NT = kLuThreadsBig, nw = NT / 64;
   __shared__ double S[16 * kLd], P[16 * kLd], sL[16 * 17];
   __shared__ int perm[kLuMidMaxn], bad;

@@ -99,6 +99,17 @@ __device__ inline bool weak_done(int weak, double* ws, const Item& it) {
   return weak && *weak_flag(ws + it.ws + extras_off(it.n), it.n) < 0;
 }
 
+// Whether the layer has failed, the same answer for every wave of the workgroup: another order of the layer may
+// set the status in the same launch, and waves that read it for themselves could part at the first barrier. For
+// kernels that set the status; in a loop, a barrier has to stand between the use of the answer and the next call.
+__device__ inline bool layer_failed(const int32_t* status, int layer) {
+  __shared__ int failed;
+  if (threadIdx.x == 0)
+    failed = __hip_atomic_load(status + layer, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+  __syncthreads();
+  return failed != 0;
+}
+
 struct BeamTask {  // one workgroup of the beam synthesis: (layer, outgoing node i, incident mu0_j)
   int32_t layer, i, j, pad;
 };
