@@ -30,6 +30,21 @@ __device__ inline double block_sum(double v, double* sred) {
   return r;
 }
 
+// Eigenvalues closer than this cannot be told apart in a matrix of Frobenius norm hnorm: copies of one multiple
+// eigenvalue, whose couplings are rounding noise.
+__device__ inline double same_eigenvalue(double hnorm) { return 8.0 * kUlp * hnorm; }
+
+// Whether a 2 x 2 block with off-diagonal entries b, c and a complex pair of imaginary part im is two such copies
+// whose noise couples them in one direction only (c = 1e-140 beside b = 1e-13 in orders with next to no
+// scattering). Taken as a pair, its eigenvector would have real and imaginary parts parallel to im / |b| (1e-60: a
+// singular eigenvector matrix, and a response of 1e10 for one of 1e-15); real eigenvalues with the
+// coupling dropped are as close to the matrix. Other blocks of copies have im / |b| above 1e-3, but for one in
+// 1e5 orders or so.
+__device__ inline bool uncoupled_copies(double b, double c, double im, double hnorm) {
+  const double most = fmax(fabs(b), fabs(c));
+  return most <= same_eigenvalue(hnorm) && im <= 1e-6 * most;
+}
+
 struct Cx {
   double re, im;
 };

@@ -1003,11 +1003,14 @@ __device__ __forceinline__ void eigen_body(const Item& it, double* base, int32_t
               sxyz[1] = (nv > 0.0) ? v1 / nv : 0.0;
               sctl[4] = kActRotate;
             } else {
-              lre[hh - 1] = lre[hh] = 0.5 * (a + d);
-              lim[hh - 1] = sqrt(-disc);
-              lim[hh] = -sqrt(-disc);
-              blk[hh - 1] = 2;
-              blk[hh] = 0;
+              const bool copies = uncoupled_copies(b, c, sqrt(-disc), hnorm);
+              if (copies) HH(hh, hh - 1) = 0.0;
+              lre[hh - 1] = copies ? a : 0.5 * (a + d);
+              lre[hh] = copies ? d : 0.5 * (a + d);
+              lim[hh - 1] = copies ? 0.0 : sqrt(-disc);
+              lim[hh] = copies ? 0.0 : -sqrt(-disc);
+              blk[hh - 1] = copies ? 1 : 2;
+              blk[hh] = copies ? 1 : 0;
               sctl[1] = hh - 2;
               sctl[2] = 0;
               sctl[4] = kActDeflated;
@@ -1561,7 +1564,7 @@ __device__ __forceinline__ void eigen_body(const Item& it, double* base, int32_t
   // unscattered Stokes components at one node, lambda = 1/mu^2), and its Schur coupling is
   // rounding noise. Its component is set to zero instead of dividing the noise by a guarded pivot,
   // which would make the copies' eigenvectors parallel.
-  const double same = 8.0 * kUlp * hnorm;
+  const double same = same_eigenvalue(hnorm);
   if constexpr (kLds) {
     // All eigenvectors advance together over T's diagonal blocks from the bottom: the block's
     // rows of T are staged in LDS (the same for every thread) and the eigenvector matrix X

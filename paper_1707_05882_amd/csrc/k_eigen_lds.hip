@@ -528,12 +528,15 @@ __device__ __forceinline__ void qr_decide(EigenLds& s, int n, QrState& q, double
     if (l == hh - 1) {
       const int h1 = hh - 1;
       if (disc < 0.0) {
+        const bool copies = uncoupled_copies(t12, t21, root, hnorm);
         if (lane == 0) {
-          s.lre[h1] = s.lre[hh] = 0.5 * (t11 + t22);
-          s.lim[h1] = root;
-          s.lim[hh] = -root;
-          s.blk[h1] = 2;
-          s.blk[hh] = 0;
+          if (copies) HH(hh, h1) = 0.0;
+          s.lre[h1] = copies ? t11 : 0.5 * (t11 + t22);
+          s.lre[hh] = copies ? t22 : 0.5 * (t11 + t22);
+          s.lim[h1] = copies ? 0.0 : root;
+          s.lim[hh] = copies ? 0.0 : -root;
+          s.blk[h1] = copies ? 1 : 2;
+          s.blk[hh] = copies ? 1 : 0;
         }
         q.hh = hh - 2;
         q.its = 0;
@@ -974,7 +977,7 @@ __device__ __forceinline__ void lds_eigen(const Item& it, double* base, int32_t*
     ex[t] = s.lre[t];
     ex[n + t] = s.lim[t];
   }
-  const double same = 8.0 * kUlp * hnorm;
+  const double same = same_eigenvalue(hnorm);
   if (n <= 64)
     eigenvectors_small(s, n, same, XT);
   else

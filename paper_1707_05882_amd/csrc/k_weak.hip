@@ -26,8 +26,7 @@
 // the orders of moderate coupling, whose clusters of four nearly equal eigenvalues it cannot separate,
 // reaches 1e-7 of the rms of F_r (against 3e-10 here), so taking those orders as well would be more
 // accurate and faster still, but would move results by that much; with the faint orders alone they
-// stay within 1e-8 of it. In the faintest orders the general solver can fail outright (a response of
-// 1e10 for one of 1e-15, in about one of 3000 layers at N = 48 and 64): those are right now.
+// stay within 1e-8 of it.
 //
 // Work split: block columns are independent, so a workgroup takes a panel of 64, 32 or 16 columns
 // (n <= 128, 256, 512: the panel fills 64 KB of LDS) and keeps it there over all steps, with no
