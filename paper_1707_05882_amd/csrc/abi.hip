@@ -753,10 +753,9 @@ static void enqueue_stacks(const LaunchSet& ls, const double* base, int32_t* lay
   if (p->base_kind != VBRDF_BASE_BLACK) {
     int64_t most = 1;  // entries of the largest Mueller base
     if (p->base_kind == VBRDF_BASE_MUELLER) most = (int64_t)p->max_M * mn * mn;
-    const int64_t chunks = (most + 256 * kBaseChunk - 1) / (256 * kBaseChunk);
-    k_stack_validate<<<(unsigned)(chunks * p->n_layers), 256, 0, s>>>(p->layers_d, p->n_layers, p->below_d,
-                                                                      p->base_kind, base, p->base_off_d,
-                                                                      layer_status);
+    const int groups = base_check_groups(most, p->n_layers);
+    k_stack_validate<<<p->n_layers * groups, 256, 0, s>>>(p->layers_d, p->n_layers, groups, p->below_d, p->base_kind,
+                                                          base, p->base_off_d, layer_status);
   }
   k_stack_status<<<(p->n_layers + 255) / 256, 256, 0, s>>>(p->n_layers, p->below_d, layer_status);
   const int xb = std::min(1024, (mn * mn + 255) / 256);

@@ -26,9 +26,10 @@ namespace vbrdf {
 constexpr double kPi = 3.141592653589793;
 
 // Base data checks: rho in [0, 1] (Lambertian), finite entries (Mueller). Only bottom
-// layers of stacks carry base data. A workgroup takes 256 kBaseChunk entries of one layer's base: bound by the
-// read of the base, which one workgroup per layer did at 15 GB/s (670 us for 24 orders at N = 40 and two layers, now 5 us).
-__global__ void k_stack_validate(const Layer* layers, int n_layers, const int32_t* below, int base_kind,
+// layers of stacks carry base data. `groups` workgroups share a layer's base, 256 kBaseChunk entries at a time: bound by
+// the read of the base, which one workgroup per layer did at 15 GB/s (670 us for 24 orders at N = 40 and two layers,
+// now 5 us).
+__global__ void k_stack_validate(const Layer* layers, int n_layers, int groups, const int32_t* below, int base_kind,
                                  const double* base, const int64_t* base_off, int32_t* status) {
   const int l = blockIdx.x % n_layers;
   if (below[l] >= 0 || base_kind == VBRDF_BASE_BLACK) return;
@@ -40,12 +41,14 @@ __global__ void k_stack_validate(const Layer* layers, int n_layers, const int32_
     const Layer ly = layers[l];
     const int64_t n = 4 * (int64_t)ly.N, cnt = (int64_t)ly.M * n * n;
     const double* b = base + base_off[l];
-    const int64_t t0 = (int64_t)(blockIdx.x / n_layers) * (256 * kBaseChunk) + threadIdx.x;
-    double v[kBaseChunk];
+    for (int64_t t0 = (int64_t)(blockIdx.x / n_layers) * (256 * kBaseChunk) + threadIdx.x; t0 < cnt;
+         t0 += (int64_t)groups * (256 * kBaseChunk)) {
+      double v[kBaseChunk];
 #pragma unroll
-    for (int u = 0; u < kBaseChunk; ++u) v[u] = t0 + 256 * u < cnt ? b[t0 + 256 * u] : 0.0;
+      for (int u = 0; u < kBaseChunk; ++u) v[u] = t0 + 256 * u < cnt ? b[t0 + 256 * u] : 0.0;
 #pragma unroll
-    for (int u = 0; u < kBaseChunk; ++u) bad |= !isfinite(v[u]);
+      for (int u = 0; u < kBaseChunk; ++u) bad |= !isfinite(v[u]);
+    }
   }
   if (bad) atomicCAS(&status[l], 0, VBRDF_E_INVALID);  // an earlier failure of the layer stays
 }

@@ -295,9 +295,16 @@ struct StackTask {
   int32_t pad;
 };
 constexpr int kMaxStackLevels = 64;
-__global__ void k_stack_validate(const Layer* layers, int n_layers, const int32_t* below, int base_kind, const double* base,
-                                 const int64_t* base_off, int32_t* status);
-constexpr int kBaseChunk = 8;  // entries of a Mueller base that a thread of k_stack_validate looks at
+__global__ void k_stack_validate(const Layer* layers, int n_layers, int groups, const int32_t* below, int base_kind,
+                                 const double* base, const int64_t* base_off, int32_t* status);
+constexpr int kBaseChunk = 8;      // entries of a Mueller base that a thread of k_stack_validate looks at at once
+// Its workgroups per layer: one for each chunk of the largest base, but in plans of many layers, most of which
+// have a small base or none, 64, which read a base of 0.5 GB in 2 ms (one workgroup: 100 ms; a workgroup for
+// each chunk: 10 ms beside 3000 layers, nearly all of it idle, and more than a launch takes beside 33000).
+__host__ __device__ inline int base_check_groups(int64_t entries, int n_layers) {
+  const int64_t chunks = (entries + 256 * kBaseChunk - 1) / (256 * kBaseChunk), few = 4096 / n_layers;
+  return (int)(chunks < 64 ? chunks : (chunks < few ? chunks : (few < 64 ? 64 : few)));
+}
 __global__ void k_stack_status(int n_layers, const int32_t* below, int32_t* status);
 __global__ void k_stack_x(const Item* items, const StackTask* tasks, const Layer* layers, const double* quad,
                           int base_kind, const double* base, double* ws, int32_t* status);
