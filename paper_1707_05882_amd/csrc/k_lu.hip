@@ -9,16 +9,18 @@
 //   A  the panel wave factors the panel, while the others give the columns right of it the update of
 //      the panel before,
 //   B  the other waves hand over the pivot rows of their tiles,
-//   C  one side solves L11 U12 = A12, a column per lane, the other writes the panel to memory,
+//   C  the panel wave solves L11 U12 = A12, a column per lane, the others write the panel to memory,
 //   D  the next panel's columns take the update A22 -= L21 U12 and go to the panel wave.
 // Row exchanges stay logical: a row keeps its place, with its multiplier zero once it has been
 // the pivot row, so that its tiles then hold its row of Uu. The operations on an element and their order
 // are those of the column by column form and of the blocked one (k_lu): all give the same bits. Bound by the
 // panel wave's chain of n columns: 560 cycles each up to n = 64 (a row per lane), 820 up to 128, 980 up to
-// 192, next to 370 for the solve of U12 and 80 to 250 for each of the other phases, by 16 columns.
+// 192, next to 370 for the solve of 64 columns of U12 and 80 to 250 for each of the other phases, by 16 columns.
 // Measured, the form before -> now: n = 32 41 -> 14 us, n = 64 81 -> 24 us, n = 128 196 -> 85 us, n = 160
-// (blocked) 220 -> 148 us; 9216 systems of n = 128 4.48 -> 1.96 ms. The sizes end where the rows of a
-// tile wave still fit its registers: at 192 both kinds of waves are at their limit of 128.
+// (blocked) 220 -> 148 us; 9216 systems of n = 128 4.48 -> 1.96 ms. The sizes end at 192, where both kinds of waves
+// are at their limit of 128 registers without private scratch, which callers that must not allocate rely on
+// (k_lu_mid at n = 160: 170 us). There a lane of the panel wave solves for one column at a time,
+// and tiles beyond the matrix are updated like the others (branches around them took registers).
 #include "vbrdf_internal.hpp"
 
 namespace vbrdf {
@@ -209,7 +211,7 @@ __device__ __forceinline__ void lu_panel(double (&a)[kPer][16], int (&pos)[kPer]
 // with registers to spare. The loads are a column ahead of their use and no more: their address waits for
 // the entries before.
 template <int kPer>
-__device__ __forceinline__ void lu_solve_wide(const double* sL, double* Ub, int ldu, int cols) {
+__device__ __forceinline__ void lu_solve(const double* sL, double* Ub, int ldu, int cols) {
   const int lane = threadIdx.x & 63;
   double x[kPer][16];
 #pragma unroll
@@ -243,35 +245,6 @@ __device__ __forceinline__ void lu_solve_wide(const double* sL, double* Ub, int 
       for (int t = 0; t < 16; ++t) Ub[t * ldu + lane + 64 * i] = x[i][t];
 }
 
-// The same for column c, by a wave that holds tiles. sL[s 16 + t] = L11(t, s). In two halves of 8 rows, whose
-// loads wait for the columns before (all issued at once they would not leave registers for the tiles).
-__device__ __forceinline__ void lu_solve(const double* sL, double* Ub, int ldu, int c) {
-  double x[8];
-  double* uc = Ub + c;
-  int z = 0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) x[t] = uc[(8 * h + t) * ldu];
-    if (h == 1)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if (s % 2 == 0) asm volatile("" : "+v"(z), "+v"(x[0]));
-        const double us = uc[s * ldu];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] = fma(-sL[z + s * 16 + 8 + t], us, x[t]);
-      }
-#pragma unroll
-    for (int s = 0; s < 7; ++s) {
-      if (s % 2 == 0) asm volatile("" : "+v"(z), "+v"(x[s]));
-#pragma unroll
-      for (int t = s + 1; t < 8; ++t) x[t] = fma(-sL[z + (8 * h + s) * 16 + 8 * h + t], x[s], x[t]);
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) uc[(8 * h + t) * ldu] = x[t];
-  }
-}
-
 // Buffer b.src[side] = P^T L Uu of the systems with n_above < n <= 16 kT (side = blockIdx.y: S' and T'
 // of the boundary solve, or U^T of the eigenpair refinement). The factor is written transposed into
 // b.dst[side], AT[j n + c] = A(c, j), so that column j of Uu (c <= j) and of L (c > j) are contiguous for
@@ -282,8 +255,8 @@ __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, dou
   const Item it = items[blockIdx.x];
   if (it.n <= n_above || it.n > 16 * kT || layer_failed(status, it.layer) || weak_done(b.skip_weak, ws, it)) return;
   constexpr int kPer = (kT + 3) / 4;
-  // who solves for U12: the panel wave, or, where its 48 columns a lane leave no registers, those with tiles
-  constexpr bool kWide = kPer < 3;
+  constexpr bool kTight = kPer == 3;         // both kinds of waves are at their limit of 128 registers
+  constexpr int kSolve = kTight ? 1 : kPer;  // columns of U12 that a lane solves for at a time
   constexpr int kLd = 16 * kT + 4;    // columns of P and T: 16 lanes a column apart spread over the banks
   constexpr int kLdu = 16 * kT + 16;  // rows of Ub: two halves of 16 lanes a row apart, likewise
   __shared__ double P[16 * kLd], T[16 * kLd], Ub[16 * kLdu];
@@ -335,26 +308,12 @@ __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, dou
       }
       __syncthreads();  // 1
       if (bad) return;
-      // the panel in the original order of rows, which the end permutes
-      auto store = [&] {
-        double* __restrict__ at = AT + (int64_t)k0 * n + lane;
-#pragma unroll 4
-        for (int c = 0; c < min(16, n - k0); ++c, at += n)
-#pragma unroll
-          for (int i = 0; i < kPer; ++i)
-            if (lane + 64 * i < n) at[64 * i] = P[c * kLd + lane + 64 * i];
-      };
-      if (p + 1 == R) {
-        if (!kWide) store();
-        break;
-      }
+      if (p + 1 == R) break;
       for (int t = lane; t < 256; t += 64)  // L11, for the solve
         sL[t] = P[(t >> 4) * kLd + perm[k0 + (t & 15)]];
       __syncthreads();  // 2
-      if constexpr (kWide)
-        lu_solve_wide<kPer>(sL, Ub, kLdu, 16 * (R - 1 - p));
-      else
-        store();
+      for (int c0 = 0; c0 < 16 * (R - 1 - p); c0 += 64 * kSolve)
+        lu_solve<kSolve>(sL, Ub + c0, kLdu, 16 * (R - 1 - p) - c0);
       __syncthreads();  // 3
       __syncthreads();  // 4
     }
@@ -371,35 +330,34 @@ __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, dou
 #pragma unroll
     for (int v = 0; v < 4; ++v) T[lr * kLd + 16 * wv + 4 * v + kq] = X[0][v];
     __syncthreads();
-    for (int p = 0; p < R; ++p) {
+    auto store = [&](int p) {  // panel p in the original order of rows, which the end permutes
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+#pragma unroll 1
+      for (int c = wv; c < min(16, n - 16 * p); c += kT)
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+          if (ln + 64 * i < n) AT[(int64_t)(16 * p + c) * n + ln + 64 * i] = P[c * kLd + ln + 64 * i];
+    };
+    // (the last panel after the loop: left from its middle, the loop would keep two copies of the tiles)
+    for (int p = 0; p + 1 < R; ++p) {
       const int rem = R - 1 - p;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));  // addresses are formed anew for each panel: kept, they would spill
+      const int lr = ln & 15, kq = ln >> 4;
       __syncthreads();  // 1
       if (bad) return;
-      if (rows && rem > 0)
+      if (rows)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int t = tpos[16 * wv + 4 * v + kq];
           if (t >= 0 && t < 16)
 #pragma unroll
             for (int j = 1; j < kT; ++j)
-              if (j <= rem) Ub[t * kLdu + 16 * (j - 1) + lr] = X[j][v];
+              if (kTight || j <= rem) Ub[t * kLdu + 16 * (j - 1) + lr] = X[j][v];
         }
-      auto store = [&] {  // as the panel wave's
-        for (int c = wv; c < min(16, n - 16 * p); c += kT)
-#pragma unroll
-          for (int i = 0; i < kPer; ++i)
-            if (lane + 64 * i < n) AT[(int64_t)(16 * p + c) * n + lane + 64 * i] = P[c * kLd + lane + 64 * i];
-      };
-      if (rem == 0) {
-        if (kWide) store();
-        break;
-      }
       __syncthreads();  // 2
-      if constexpr (kWide) {
-        store();
-      } else {
-        if (const int c = 64 * wv + lane; c < 16 * rem) lu_solve(sL, Ub, kLdu, c);
-      }
+      store(p);
       __syncthreads();  // 3
       double l[4];
       const int late = tpos[16 * wv + lr];
@@ -422,10 +380,18 @@ __global__ __launch_bounds__(64 * (kT + 1)) void k_lu_reg(const Item* items, dou
       if (rows)
 #pragma unroll
         for (int j = 2; j < kT; ++j)
-          if (j <= rem) update(j);
+          if (kTight || j <= rem) update(j);
+      // The tiles are copied now, in another block of the compiled loop than the instructions that wrote them, where
+      // the compiler has left out the wait states between the two.
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 15\n\ts_nop 3");
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j + 1 < kT; ++j) X[j] = X[j + 1];
+      for (int j = 1; j + 1 < kT; ++j) X[j] = X[j + 1];
     }
+    __syncthreads();  // 1
+    if (bad) return;
+    store(R - 1);
   }
   __syncthreads();  // the factor in the original order of rows is in memory, the final order in perm
   double* id = ex + (4 + which) * (int64_t)n;
