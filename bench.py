@@ -77,12 +77,23 @@ def stage_kernels(stage):
     return [f"k_{stage}"]
 
 
+def source_hash(kernel):
+    """First 16 hex digits of the sha256 of what a kernel is compiled from: its source file and every
+    header beside it (device code is shared through them)."""
+    import hashlib
+
+    csrc = os.path.join(ROOT, "paper_1707_05882_amd", "csrc")
+    h = hashlib.sha256()
+    for part in [KERNEL_SOURCE[kernel]] + sorted(f for f in os.listdir(csrc) if f.endswith(".hpp")):
+        with open(os.path.join(csrc, part), "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()[:16]
+
+
 def measured_traffic(kernels, workload):
     """HBM bytes per launch of the stage made of `kernels`, summed over the kernels recorded in the
     byte counters of this workload (profiles/traffic_<workload>.txt); None when there is no record
     or a recorded kernel's sources have changed since it was taken."""
-    import hashlib
-
     path = os.path.join(ROOT, "profiles", f"traffic_{workload}.txt")
     if not os.path.exists(path) or any(k not in KERNEL_SOURCE for k in kernels):
         return None
@@ -96,11 +107,7 @@ def measured_traffic(kernels, workload):
         return None
     total = 0.0
     for k, (sha_rec, nbytes) in rec.items():
-        h = hashlib.sha256()
-        for part in (KERNEL_SOURCE[k], "vbrdf_internal.hpp"):
-            with open(os.path.join(ROOT, "paper_1707_05882_amd", "csrc", part), "rb") as fh:
-                h.update(fh.read())
-        if h.hexdigest()[:16] != sha_rec:
+        if source_hash(k) != sha_rec:
             return None
         total += nbytes
     return total
