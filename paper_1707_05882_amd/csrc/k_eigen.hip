@@ -111,6 +111,8 @@ __device__ __forceinline__ void hess_batches(int i0, int len, int step, Load loa
   }
 }
 
+constexpr int kEigenBigLds = 88 * (89 + 97);  // doubles of k_eigen_big's LDS buffer: a window and its transformation
+
 // H <- H (I - tau v v^T) of one step of the reduction, v = (1, scal sv[1 .. len - 1]) on columns k + 1 .., H in
 // global memory, a row per thread. A thread's dot product runs over its row from left to right; read by
 // the row's thread itself, a wave's load would touch 64 lines, so tiles of 16 columns go through LDS. The
@@ -120,7 +122,7 @@ __device__ void hess_right(double* __restrict__ H, int n, int k, int len, double
                            double* sbuf) {
   constexpr int kW = 16, kLd = kW + 1, kPer = kMaxn * kW / kEigenThreads, kRows = kEigenThreads / kW;
   static_assert(kEigenThreads >= kMaxn, "a row per thread");
-  static_assert(kMaxn * (kLd + 2) <= kLdsMaxn * (kLdsMaxn + 1), "tile, y and v fit the LDS buffer");
+  static_assert(kMaxn * (kLd + 2) <= kEigenBigLds, "tile, y and v fit the LDS buffer");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   double* ys = sbuf + kMaxn * kLd;
   double* vs = ys + kMaxn;
@@ -187,6 +189,7 @@ constexpr int kWinLd = kWin + 1;  // LDS row stride of the window
 // all 64 lanes in one bank)
 constexpr int kWinU = 97;
 static_assert(kWin % 4 == 0 && kWinU >= (kWin + 15) / 16 * 16 && kWinU % 2 == 1, "MFMA tiling of the window update");
+static_assert(kEigenBigLds == kWin * kWinLd + kWin * kWinU);
 static_assert(kWin * kWinLd + kWin * kWinU <= kLdsMaxn * (kLdsMaxn + 1) + 3 * 64,
               "window and U fit the LDS buffer of the LDS-resident path");
 static_assert(kWin > 4 * kMaxBulges + 4, "a window holds the whole bulge chain and lets it advance");
@@ -2056,7 +2059,7 @@ __global__ __launch_bounds__(kEigenThreads) void k_eigen_big(const Item* items, 
                                                               int sweep_cap, const int32_t* order, int weak) {
   const Item it = items[order ? order[blockIdx.x] : blockIdx.x];
   if (it.n <= kLdsMaxn || layer_failed(status, it.layer) || weak_done(weak, ws, it)) return;
-  __shared__ double sbuf[kWin * kWinLd + kWin * kWinU];
+  __shared__ double sbuf[kEigenBigLds];
   __shared__ double srefl[2 * 3 * kMaxn];
   __shared__ double sred[16];
   __shared__ int sctl[8];
