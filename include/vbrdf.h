@@ -28,6 +28,13 @@
  *     a reflecting base (vbrdf_plan_desc.base); a layer's F_r is then the BRDF of its sub-stack,
  *     from that layer down to the base.
  *
+ * Accuracy and the rest of the plan: an order is solved by the general eigensolver or, where its scattering is weak,
+ * by an iteration. Plans of more than 256 orders in all, and plans with a layer of N > 64, use the iteration for every
+ * weakly coupled order of layers with N <= 32 and for the faintest orders of larger ones; other plans,
+ * plans with VBRDF_FLAG_SAVE_FOR_BACKWARD and plans with a qr_sweep_cap do not. Both are within the library's
+ * accuracy, but their last digits differ: a layer's F_r is the same bit for bit from call to call of one
+ * plan and for every schedule, but not always between plans that differ in their other layers or flags.
+ *
  * Memory ownership: every pointer passed to these functions stays owned by the caller. Device
  * pointers must stay valid until the enqueued work on the given stream has completed. The plan
  * owns its device workspace (released by vbrdf_plan_destroy).
